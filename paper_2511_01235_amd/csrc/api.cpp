@@ -90,6 +90,7 @@ struct mf_graph {
     int32_t round_min = 2;    // ... and at least this many (option round_min)
     bool incremental_rounds = true;  // rounds take their worklist from the previous one plus activations
     int64_t narrow_max = 4096;       // BFS frontiers of up to this many slots run in one workgroup (0: never)
+    int narrow_lds = 0;              // LDS those launches may use
     int64_t medium_max = 65536;      // ... up to this many in one cooperative launch of a few workgroups
     int32_t rn_limit = 2048;         // worklists of up to this many vertices run rounds in one workgroup
     bool bfs_cap = true;             // solve relabels stop once every vertex with excess has a height
@@ -451,6 +452,9 @@ void apply_loop_options(mf_graph* g, const mf_options& o) {
     auto on = [](int32_t v, bool dflt) { return v > 0 ? true : v < 0 ? false : dflt; };
     g->first_chunk = o.bfs_first_chunk > 0 ? o.bfs_first_chunk : 7;
     g->narrow_max = o.bfs_narrow_slots < 0 ? 0 : o.bfs_narrow_slots > 0 ? o.bfs_narrow_slots : 4096;
+    g->narrow_max = g->narrow_lds == 0
+                        ? 0
+                        : std::min<int64_t>(g->narrow_max, mf::narrow_map_slots(g->bits.nwords, g->narrow_lds));
     g->medium_max = o.bfs_medium_slots < 0 ? 0 : o.bfs_medium_slots > 0 ? o.bfs_medium_slots : 65536;
     g->medium_blocks = o.bfs_medium_blocks > 0 ? o.bfs_medium_blocks : 16;
     // mid-size frontiers need cooperative launch (every block resident)
@@ -632,8 +636,8 @@ mf_status global_relabel(mf_graph* g, const LoopMode& m, int64_t* levels_out, in
     for (;;) {
         if (narrow) {
             timed(g, m.L, mf::KC_GRS, [&] {
-                mf::launch_gr_narrow(m.dg, level, m.L.q[0], m.L.q[1], m.L.ctr, m.L.bits, g->narrow_max, m.forward,
-                                     st);
+                mf::launch_gr_narrow(m.dg, level, m.L.q[0], m.L.q[1], m.L.ctr, m.L.bits, g->narrow_max,
+                                     g->narrow_lds, m.forward, st);
             });
             MF_HIP(hipGetLastError());
             mf_status rc = read_lane(g, m.L);
@@ -1695,6 +1699,7 @@ mf_status mf_graph_load(int32_t n, int64_t m, const int32_t* src, const int32_t*
         g->coop_ok = hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop;
     }
     g->cus = cus;
+    g->narrow_lds = mf::narrow_lds_bytes(dev);
     apply_loop_options(g, o);
     g->dg.n = n;
     g->dg.s = s;

@@ -113,41 +113,47 @@ __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long x)
     return ((unsigned long long)hi << 32) | lo;
 }
 
-__device__ __forceinline__ long long wave_sum_i64(long long x) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, WAVE);
+// Inclusive prefix sums over the wave by the same DPP steps (a lane without a
+// source adds 0): six register moves instead of six trips through LDS.
+template <int CTRL, int ROW_MASK = 0xF>
+__device__ __forceinline__ unsigned dpp_add_step(unsigned x) {
+    return x + (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xF, false);
+}
+template <int CTRL, int ROW_MASK = 0xF>
+__device__ __forceinline__ unsigned long long dpp_add_step(unsigned long long x) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, ROW_MASK, 0xF, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, ROW_MASK, 0xF, false);
+    return x + (((unsigned long long)hi << 32) | lo);
+}
+template <class T>
+__device__ __forceinline__ T wave_incl_add(T x) {
+    x = dpp_add_step<0x111>(x);
+    x = dpp_add_step<0x112>(x);
+    x = dpp_add_step<0x114>(x);
+    x = dpp_add_step<0x118>(x);
+    x = dpp_add_step<0x142, 0xA>(x);
+    x = dpp_add_step<0x143, 0xC>(x);
     return x;
+}
+__device__ __forceinline__ unsigned lane63(unsigned x) { return (unsigned)__builtin_amdgcn_readlane((int)x, 63); }
+__device__ __forceinline__ unsigned long long lane63(unsigned long long x) {
+    return ((unsigned long long)lane63((unsigned)(x >> 32)) << 32) | lane63((unsigned)x);
 }
 
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, WAVE);
-    return x;
-}
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x) { return lane63(wave_incl_add(x)); }
+__device__ __forceinline__ long long wave_sum_i64(long long x) { return (long long)wave_sum_u64((unsigned long long)x); }
 
 // Exclusive prefix sum over the wave; *total gets the wave sum.
 __device__ __forceinline__ int wave_excl_scan(int x, int* total) {
-    int lane = lane_id();
-    int v = x;
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) {
-        int y = __shfl_up(v, d, WAVE);
-        if (lane >= d) v += y;
-    }
-    *total = __shfl(v, WAVE - 1, WAVE);
-    return v - x;
+    const unsigned v = wave_incl_add((unsigned)x);
+    *total = (int)lane63(v);
+    return (int)v - x;
 }
 
 __device__ __forceinline__ long long wave_excl_scan64(long long x, long long* total) {
-    int lane = lane_id();
-    long long v = x;
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) {
-        long long y = __shfl_up(v, d, WAVE);
-        if (lane >= d) v += y;
-    }
-    *total = __shfl(v, WAVE - 1, WAVE);
-    return v - x;
+    const unsigned long long v = wave_incl_add((unsigned long long)x);
+    *total = (long long)lane63(v);
+    return (long long)v - x;
 }
 
 // Append one item per lane with pred set to list[*counter ...] using one
@@ -930,70 +936,271 @@ __global__ void __launch_bounds__(BS) k_gr_level(DevGraph g, int lv, const int2*
     gr_level_step<FWD, BS>(hw_par(), g, lv, qin, qout, ctr, bits, tune, tune.lds ? s_dyn : nullptr);
 }
 
+// Barrier of a workgroup whose waves share LDS only: it does not wait for
+// their global stores (half a microsecond each), which nothing in the
+// workgroup reads back.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Thin frontiers (deep BFS, e.g. grids): one workgroup runs top-down levels
-// back to back with workgroup barriers only, from level lv0 while each
-// frontier covers at most max_slots slots.  It stops at the first empty level
-// (the BFS is over) or at a level whose frontier is larger (not processed),
-// and leaves in ctr->levels the level to continue from.  The frontier bitmaps
-// are not kept up to date here (top-down needs only the visited bitmap); the host
+// back to back from level lv0 while each frontier covers at most max_slots
+// slots.  It stops at the first empty level (the BFS is over), at a capped
+// relabel's stop, or at a level whose frontier is larger (not processed), and
+// leaves in ctr->levels the level to continue from.
+//
+// A level is bound by its chain of dependent accesses, not by bandwidth, so
+// everything a level hands to the next stays in LDS: `map` lists the slots of
+// the frontier's rows one by one (written by the lane that labels a vertex:
+// no queue entry to read, no prefix sum, no search), `list` its vertices,
+// and with LBM the visited bitmap is in LDS too (claimed there, no global
+// atomic).  What is left of the chain is a slot's {col, res, capsum} and then
+// the labelled vertex's row bounds and excess: two trips to memory a level.
+// Stores complete in half a microsecond and a wave's later loads count as
+// done only after its earlier stores, so the waves that scan store nothing:
+// the last waves of the workgroup write the heights of the vertices labelled
+// one level before, and the barrier between levels waits for LDS only.
+// Measured on a 256 x 256 grid: 6.8 us a level before (nine trips, five
+// barriers that drained stores), 2.3 now.
+//
+// LBM needs the bitmap beside maps and lists in LDS (the host checks);
+// without it the visited words are tested and claimed in global memory.  The
+// global queue is written at a hand-back only; the frontier bitmaps are not
+// kept up to date here (top-down needs only the visited bitmap): the host
 // rebuilds the current one before multi-block levels continue.
 constexpr int NARROW_BLOCK = 1024;
+constexpr int NARROW_SCAN = 768;         // threads that scan; the others write heights
+constexpr int NARROW_MAP = 8192;         // slots of a frontier at most
+constexpr int NARROW_MAP_MIN = 4096;     // ... and at least, with the bitmap beside the maps and lists
+constexpr int NARROW_STATIC = 128;       // the kernel's other LDS
+constexpr int NARROW_ROW = 32;           // longer rows are written to the map by their whole wave
 
-template <bool FWD>
+// One level's {slots, vertices} in an LDS word, slots in the high half.
+// Called by a whole wave: up to U vertices per lane (vs[k], slots beg[k] ..
+// beg[k] + len[k], none where len[k] is 0) go behind what *front counts.
+// (A frontier of more than cap slots is handed back from its list: its map
+// may be cut short.)
+template <int U>
+__device__ __forceinline__ void narrow_put(const int (&vs)[U], const int (&beg)[U], const int (&len)[U], int* map,
+                                           int* list, int cap, unsigned long long* front) {
+    unsigned sl = 0, cnt = 0;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        sl += (unsigned)len[k];
+        cnt += len[k] > 0 ? 1u : 0u;
+    }
+    const unsigned icnt = wave_incl_add(cnt);
+    const unsigned tcnt = lane63(icnt);
+    if (tcnt == 0) return;  // wave-uniform
+    const unsigned isl = wave_incl_add(sl);
+    unsigned long long base = 0;
+    if (lane_id() == 0) base = atomicAdd(front, ((unsigned long long)lane63(isl) << 32) | tcnt);
+    base = (unsigned long long)bcast64((int64_t)base);
+    unsigned so = (unsigned)(base >> 32) + isl - sl;
+    unsigned at = (unsigned)base + icnt - cnt;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        if (len[k] > 0) list[at++] = vs[k];
+        if (len[k] <= NARROW_ROW)
+            for (int i = 0; i < len[k]; ++i)
+                if (so + i < (unsigned)cap) map[so + i] = beg[k] + i;
+        unsigned long long lm = __ballot(len[k] > NARROW_ROW);
+        while (lm) {  // wave-uniform
+            const int l = __ffsll((long long)lm) - 1;
+            lm &= lm - 1;
+            const int b = __builtin_amdgcn_readlane(beg[k], l), n = __builtin_amdgcn_readlane(len[k], l);
+            const unsigned o = (unsigned)__builtin_amdgcn_readlane((int)so, l);
+            for (int i = lane_id(); i < n && o + i < (unsigned)cap; i += WAVE) map[o + i] = b + i;
+        }
+        so += (unsigned)len[k];
+    }
+}
+
+template <bool FWD, bool LBM, int U>
+__device__ __forceinline__ int narrow_slots(const DevGraph& g, const GrBits& bits, int fs, const int* map, int* next,
+                                            int* list, int cap, unsigned* s_vis, unsigned long long* front,
+                                            int* s_disc) {
+    const int tid = threadIdx.x;
+    int found = 0;
+    for (int base = 0; base < fs; base += U * NARROW_SCAN) {
+        int2 c[U];
+        int32_t sum[U], r[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {  // every load of the U slots is issued before the first is used
+            const int j = map[min(base + k * NARROW_SCAN + tid, fs - 1)];
+            c[k] = g.cr[j];
+            sum[k] = FWD ? 0 : g.capsum[j];
+        }
+        bool won[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            r[k] = base + k * NARROW_SCAN + tid < fs ? (FWD ? c[k].y : sum[k] - c[k].y) : 0;
+            // the pinned vertex and the other side are marked visited at init
+            const int v = c[k].x;
+            const unsigned bit = 1u << (v & 31);
+            if (LBM) won[k] = r[k] > 0 && !(atomicOr(&s_vis[v >> 5], bit) & bit);
+            else won[k] = r[k] > 0 && !bit_of(bits.visited, v);
+        }
+        if (!LBM) {
+            unsigned old[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                old[k] = ~0u;
+                if (won[k]) old[k] = atomicOr(&bits.visited[c[k].x >> 5], 1u << (c[k].x & 31));
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) won[k] = won[k] && !(old[k] >> (c[k].x & 31) & 1u);
+        }
+        int vs[U], beg[U], len[U];
+        int64_t ex[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            vs[k] = c[k].x;
+            beg[k] = 0;
+            len[k] = 0;
+            ex[k] = 0;
+            if (won[k]) {
+                beg[k] = g.row_ptr[vs[k]];
+                len[k] = g.row_len[vs[k]];
+                if (g.bfs_cap) ex[k] = ld_e(g.e, vs[k]);
+            }
+        }
+        narrow_put<U>(vs, beg, len, next, list, cap, front);
+        int disc = 0;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            disc += ex[k] > 0 && vs[k] != g.s && vs[k] != g.t;
+            found += won[k];
+        }
+        if (disc) atomicAdd(s_disc, disc);
+    }
+    return found;
+}
+
+template <bool FWD, bool LBM>
 __global__ void __launch_bounds__(NARROW_BLOCK) k_gr_narrow(DevGraph g, int lv0, int2* q0, int2* q1,
-                                                            DevCounters* ctr, GrBits bits, long long max_slots) {
-    __shared__ unsigned long long s_front;
-    __shared__ int s_stop;
-    const Par P{0, 1};
-    int lv = lv0;
-    // one thread reads the level's counts and takes the capped relabel's
-    // decision (as gr_level_step does); the block follows it
-    auto level_counts = [&](int l) {
-        if (threadIdx.x == 0) {
-            s_front = __hip_atomic_load(&ctr->front[l % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_stop = 0;
-            if (g.bfs_cap) {
-                const int labelled = excess_labelled(ctr, l);
-                s_stop = labelled >= excess_total(ctr);
-                ctr->bfs_cum[l % 3] = labelled;
-                ctr->bfs_disc[(l + 2) % 3] = 0;
-            }
-        }
-    };
-    level_counts(lv);
-    if (threadIdx.x == 0 && lv == 0) ctr->seed_front = s_front;
+                                                            DevCounters* ctr, GrBits bits, long long max_slots,
+                                                            int map_cap) {
+    extern __shared__ unsigned s_dyn[];
+    __shared__ unsigned long long s_front[3];  // a ring by level
+    __shared__ int s_disc[3];                  // vertices with excess labelled, by level
+    __shared__ unsigned s_pieces;              // hand-back: queue entries
+    int* const maps = reinterpret_cast<int*>(s_dyn);
+    int* const lists = maps + 2 * map_cap;
+    unsigned* const s_vis = s_dyn + 4 * map_cap;
+    const int tid = threadIdx.x;
+    const bool cap = g.bfs_cap != 0;
+    const unsigned long long front0 = ctr->front[lv0 % 3];
+    const int cnt0 = (int)(unsigned)(front0 & 0xFFFFFFFFull);
+    long long mu = ctr->unv[(lv0 + 2) % 3];  // unvisited slots, as the direction rule keeps them
+    int lab = cap ? excess_labelled(ctr, lv0) : 0;
+    const int total = cap ? excess_total(ctr) : INT_MAX;
+    if (max_slots > map_cap) max_slots = map_cap;
+    if (tid == 0 && lv0 == 0) ctr->seed_front = front0;
+    if (cnt0 == 0 || (long long)(front0 >> 32) > max_slots) {
+        if (tid == 0) ctr->levels = lv0;
+        return;
+    }
+    if (LBM)
+        for (int i = tid; i < bits.nwords; i += NARROW_BLOCK) s_vis[i] = bits.visited[i];
+    if (tid < 3) {
+        s_front[tid] = 0;
+        s_disc[tid] = 0;
+    }
+    if (tid == 0) s_pieces = 0;
     __syncthreads();
-    for (; lv <= g.n; ++lv) {
-        const int2* qin = (lv & 1) ? q1 : q0;
-        int2* qout = (lv & 1) ? q0 : q1;
-        const unsigned long long front = s_front;
-        const int cnt = (int)(unsigned)(front & 0xFFFFFFFFull);
-        // over (empty frontier), or a frontier with too many slots for one
-        // workgroup: the multi-block levels take it
-        if (cnt == 0 || (long long)(front >> 32) > max_slots) break;
-        // a capped relabel that has labelled every vertex with excess stops
-        if (s_stop) {
-            if (threadIdx.x == 0) {
-                ctr->bfs_capped = lv + 1;  // the height of every vertex not reached
-                ctr->front[lv % 3] = 0;
+    {   // the incoming frontier's slots (its heights are written)
+        const int2* qin = (lv0 & 1) ? q1 : q0;
+        for (int k0 = 0; k0 < cnt0; k0 += NARROW_BLOCK) {
+            int vs[1] = {0}, beg[1] = {0}, len[1] = {0};
+            if (k0 + tid < cnt0) {
+                const int2 ent = qin[k0 + tid];
+                vs[0] = ent.x;
+                beg[0] = g.row_ptr[ent.x] + ent.y;
+                len[0] = min(g.row_len[ent.x] - ent.y, GR_CHUNK);
             }
-            break;
+            narrow_put<1>(vs, beg, len, maps + (lv0 & 1) * map_cap, lists + (lv0 & 1) * map_cap, map_cap,
+                          &s_front[lv0 % 3]);
         }
-        __syncthreads();  // s_front is rewritten below
-        if (threadIdx.x == 0) {
-            ctr->front[(lv + 2) % 3] = 0;
-            // unvisited slots after this level's frontier, as the direction rule keeps them
-            long long fs = (long long)(ctr->front[lv % 3] >> 32);
-            ctr->unv[lv % 3] = ctr->unv[(lv + 2) % 3] - fs;
+    }
+    unsigned long long scanned = 0, found = 0, f = 0;
+    int lv = lv0, mode = 0;
+    for (;;) {
+        lds_barrier();  // the level's map, list and counts are complete
+        f = s_front[lv % 3];
+        const int fs = (int)(f >> 32);
+        if (lv > lv0) lab += s_disc[lv % 3];
+        // 1: the BFS is over; 2: a capped relabel that has labelled every
+        // vertex with excess; 3: a frontier with too many slots for here
+        if ((unsigned)f == 0) mode = 1;
+        else if (lab >= total) mode = 2;
+        else if ((long long)(f >> 32) > max_slots || lv > g.n) mode = 3;
+        if (mode) break;
+        if (tid == 0) {  // (last read before the barrier above)
+            s_front[(lv + 2) % 3] = 0;
+            s_disc[(lv + 2) % 3] = 0;
         }
-        __syncthreads();
-        gr_level_body<FWD, NARROW_BLOCK, false>(P, g, lv, cnt, qin, qout, ctr, bits, false, false, false, nullptr,
-                                                KC_GRS);
-        __syncthreads();
-        level_counts(lv + 1);
+        mu -= fs;
+        const int* map = maps + (lv & 1) * map_cap;
+        if (tid >= NARROW_SCAN) {
+            if (lv > lv0) {
+                const int* in = lists + (lv & 1) * map_cap;
+                for (int i = tid - NARROW_SCAN; i < (int)(unsigned)f; i += NARROW_BLOCK - NARROW_SCAN) g.h[in[i]] = lv;
+            }
+        } else {
+            int* next = maps + ((lv + 1) & 1) * map_cap;
+            int* list = lists + ((lv + 1) & 1) * map_cap;
+            unsigned long long* nf = &s_front[(lv + 1) % 3];
+            int* nd = &s_disc[(lv + 1) % 3];
+            if (fs <= NARROW_SCAN)
+                found += narrow_slots<FWD, LBM, 1>(g, bits, fs, map, next, list, map_cap, s_vis, nf, nd);
+            else if (fs <= 2 * NARROW_SCAN)
+                found += narrow_slots<FWD, LBM, 2>(g, bits, fs, map, next, list, map_cap, s_vis, nf, nd);
+            else
+                found += narrow_slots<FWD, LBM, 4>(g, bits, fs, map, next, list, map_cap, s_vis, nf, nd);
+        }
+        scanned += fs;
+        ++lv;
+    }
+    if (lv > lv0) {  // the last level's heights, and its queue if it is handed back
+        const int* in = lists + (lv & 1) * map_cap;
+        int2* q = (lv & 1) ? q1 : q0;
+        for (int i = tid; i < (int)(unsigned)f; i += NARROW_BLOCK) {
+            const int v = in[i];
+            g.h[v] = lv;
+            if (mode == 3) {
+                const int len = g.row_len[v];
+                unsigned p = atomicAdd(&s_pieces, (unsigned)(len + GR_CHUNK - 1) / GR_CHUNK);
+                for (int a = 0; a < len; a += GR_CHUNK) q[p++] = make_int2(v, a);
+            }
+        }
+        if (LBM && mode == 3)
+            for (int i = tid; i < bits.nwords; i += NARROW_BLOCK) bits.visited[i] = s_vis[i];
         __syncthreads();
     }
-    if (threadIdx.x == 0) ctr->levels = lv;
+    if (tid == 0) {
+        // the counters the other level kernels read, as they would have left them
+        const unsigned long long back = lv == lv0 ? front0 : (f >> 32 << 32) | s_pieces;
+        ctr->front[lv % 3] = mode == 3 ? back : 0ull;
+        ctr->front[(lv + 1) % 3] = 0;
+        ctr->front[(lv + 2) % 3] = 0;
+        if (mode == 2) ctr->bfs_capped = lv + 1;  // the height of every vertex not reached (or more)
+        ctr->unv[(lv + 2) % 3] = mu;
+        if (cap && lv > lv0) {
+            ctr->bfs_cum[(lv + 2) % 3] = lab;
+            ctr->bfs_disc[lv % 3] = 0;
+            ctr->bfs_disc[(lv + 1) % 3] = 0;
+        }
+        ctr->levels = lv;
+    }
+    if (g.count_bytes) {
+        // per slot: col + res (8), capsum (4), the visited word (4); per
+        // labelled vertex its height, row bounds and excess
+        const unsigned long long b = wave_sum_u64((tid == 0 ? 16ull * scanned : 0ull) + 24ull * found);
+        if (lane_id() == 0) add_bytes(g, KC_GRS, b);
+    }
 }
 
 // The frontier bitmap of the current level from its queue entries.
@@ -3085,10 +3292,36 @@ void launch_gr_level(const DevGraph& g, int level, const int2* qin, int2* qout, 
     }
 }
 
+int narrow_lds_bytes(int device) {
+    int max_lds = 0;
+    if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess) return 0;
+    const int bytes = max_lds - NARROW_STATIC;
+    if (bytes < 16 * NARROW_MAP) return 0;
+    const void* fns[] = {reinterpret_cast<const void*>(&k_gr_narrow<false, false>),
+                         reinterpret_cast<const void*>(&k_gr_narrow<false, true>),
+                         reinterpret_cast<const void*>(&k_gr_narrow<true, false>),
+                         reinterpret_cast<const void*>(&k_gr_narrow<true, true>)};
+    for (const void* f : fns)
+        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return 0;
+    return bytes;
+}
+
+// slots that fit each of two maps and lists with the visited bitmap beside them in LDS
+static int narrow_room(int nwords, int lds_bytes) { return (lds_bytes - 4 * nwords) / 16; }
+
+int narrow_map_slots(int nwords, int lds_bytes) {
+    const int room = narrow_room(nwords, lds_bytes);
+    return room >= NARROW_MAP_MIN ? std::min(room, NARROW_MAP) : NARROW_MAP;
+}
+
 void launch_gr_narrow(const DevGraph& g, int lv0, int2* q0, int2* q1, DevCounters* ctr, const GrBits& bits,
-                      long long max_slots, bool forward, hipStream_t st) {
-    if (forward) k_gr_narrow<true><<<1, NARROW_BLOCK, 0, st>>>(g, lv0, q0, q1, ctr, bits, max_slots);
-    else k_gr_narrow<false><<<1, NARROW_BLOCK, 0, st>>>(g, lv0, q0, q1, ctr, bits, max_slots);
+                      long long max_slots, int lds_bytes, bool forward, hipStream_t st) {
+    const bool lbm = narrow_room(bits.nwords, lds_bytes) >= NARROW_MAP_MIN;
+    const int map = (int)std::min<long long>(narrow_map_slots(bits.nwords, lds_bytes), std::max(1ll, max_slots));
+    const size_t shm = 16 * (size_t)map + (lbm ? 4 * (size_t)bits.nwords : 0);
+    auto fn = forward ? (lbm ? k_gr_narrow<true, true> : k_gr_narrow<true, false>)
+                      : (lbm ? k_gr_narrow<false, true> : k_gr_narrow<false, false>);
+    fn<<<1, NARROW_BLOCK, shm, st>>>(g, lv0, q0, q1, ctr, bits, max_slots, map);
 }
 
 void launch_frontier_bitmap(const int2* q, int cnt, const GrBits& bits, int level, hipStream_t st) {

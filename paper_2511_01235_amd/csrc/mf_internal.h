@@ -321,7 +321,11 @@ void launch_batch_repair_multi(GraphSlot* slots, GraphUpdates* gu, const int32_t
 void launch_batch_cleanup_multi(GraphUpdates* gu, int num, hipStream_t st);
 // thin-frontier BFS levels in one workgroup; ctr->levels = the level to continue from
 void launch_gr_narrow(const DevGraph& g, int lv0, int2* q0, int2* q1, DevCounters* ctr, const GrBits& bits,
-                      long long max_slots, bool forward, hipStream_t st);
+                      long long max_slots, int lds_bytes, bool forward, hipStream_t st);
+// dynamic LDS those launches may use on `device` (0: too little, never launch them)
+int narrow_lds_bytes(int device);
+// the largest frontier they take for bitmaps of nwords words
+int narrow_map_slots(int nwords, int lds_bytes);
 // BFS levels from lv0 in one cooperative launch of `grid` 1024-thread blocks
 // while the frontier covers at most max_slots slots (ctr->levels: where to
 // continue; ctr->bar_err set if a grid barrier gave up)
