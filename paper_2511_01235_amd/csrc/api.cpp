@@ -90,7 +90,7 @@ struct mf_graph {
     int32_t round_min = 2;    // ... and at least this many (option round_min)
     bool incremental_rounds = true;  // rounds take their worklist from the previous one plus activations
     int64_t narrow_max = 4096;       // BFS frontiers of up to this many slots run in one workgroup (0: never)
-    int narrow_lds = 0;              // LDS those launches may use
+    int narrow_lds = 0, rn_lds = 0;  // LDS those launches, and the one-workgroup rounds, may use
     int64_t medium_max = 65536;      // ... up to this many in one cooperative launch of a few workgroups
     int32_t rn_limit = 2048;         // worklists of up to this many vertices run rounds in one workgroup
     bool bfs_cap = true;             // solve relabels stop once every vertex with excess has a height
@@ -464,6 +464,7 @@ void apply_loop_options(mf_graph* g, const mf_options& o) {
     g->round_min = o.round_min > 0 ? o.round_min : 2;
     g->round_max = o.round_max > 0 ? o.round_max : 4096;
     g->rn_limit = o.round_narrow < 0 ? 0 : o.round_narrow > 0 ? o.round_narrow : 2048;
+    g->rn_limit = g->rn_lds == 0 ? 0 : std::min(g->rn_limit, mf::rounds_narrow_max());
     g->bfs_cap = on(o.bfs_cap, true);
     g->incremental_rounds = !on(o.round_scan, false);
     g->queue_rounds = on(o.queue_rounds, true);
@@ -1274,19 +1275,15 @@ mf_status run_loop(mf_graph* g, const LoopMode& m_in, int64_t* value) {
             // many per launch, until the list grows or empties
             if (thin(cnt)) R = std::max<int64_t>(R, THIN_ROUNDS_MIN);
             if (thin(cnt) && R - done >= 4) {
-                int32_t* other[3];
-                for (int b = 0; b < 3; ++b) other[b] = cur[b] == m.L.wl[b] ? g->wlb[b] : m.L.wl[b];
                 const int most = (int)std::min<int64_t>(R - done, INT_MAX / 2);
-                count_epochs(g, st, most);
-                mf::launch_rounds_narrow(rm.dg, cur, other, g->mark, g->mark + g->n, m.L.ctr, kc_for_bin(g, 0), most,
-                                         g->rn_limit, st);
+                count_epochs(g, st, most + 1);
+                mf::launch_rounds_narrow(rm.dg, cur, g->mark, g->mark + g->n, m.L.ctr, kc_for_bin(g, 0), most,
+                                         g->rn_limit, g->rn_lds, st);
                 mf::launch_zero_act(m.L.ctr, st);  // the last round's activations are in the new list
                 MF_HIP(hipGetLastError());
                 rc = read_lane(g, m.L);
                 if (rc != MF_OK) return rc;
                 if (c.rn_rounds > 0) {
-                    if (c.rn_set)
-                        for (int b = 0; b < 3; ++b) cur[b] = other[b];
                     done += c.rn_rounds;
                     rounds += c.rn_rounds;
                     if (c.wl[3] == 0) {
@@ -1700,6 +1697,7 @@ mf_status mf_graph_load(int32_t n, int64_t m, const int32_t* src, const int32_t*
     }
     g->cus = cus;
     g->narrow_lds = mf::narrow_lds_bytes(dev);
+    g->rn_lds = mf::rounds_narrow_lds_bytes(dev);
     apply_loop_options(g, o);
     g->dg.n = n;
     g->dg.s = s;

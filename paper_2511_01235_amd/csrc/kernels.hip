@@ -55,13 +55,40 @@ __device__ __forceinline__ int64_t ld_e(const int64_t* e, int v) {
 __device__ __forceinline__ void add_e(int64_t* e, int v, int64_t d) {
     __hip_atomic_fetch_add(&e[v], d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// v receives d > 0; when activations are tracked and v's excess turns
-// positive, v goes on the activation list
-__device__ __forceinline__ void gain_e(const DevGraph& g, int v, int64_t d) {
-    int64_t old = __hip_atomic_fetch_add(&g.e[v], d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (g.act && old <= 0 && old + d > 0) {
-        int k = atomicAdd(g.act_cnt, 1);
+__device__ __forceinline__ int64_t add_e_old(int64_t* e, int v, int64_t d) {
+    return __hip_atomic_fetch_add(&e[v], d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Where a kernel puts the vertices whose excess turns positive: nowhere, the
+// graph's activation list (if it has one), or a list in LDS.
+struct ActNone {
+    __device__ bool on(const DevGraph&) const { return false; }
+    __device__ void add(const DevGraph&, int) const {}
+};
+struct ActList {
+    __device__ bool on(const DevGraph& g) const { return g.act != nullptr; }
+    __device__ void add(const DevGraph& g, int v) const {
+        const int k = atomicAdd(g.act_cnt, 1);
         if (k < g.act_cap) g.act[k] = v;
+    }
+};
+struct ActLds {
+    int* list;
+    int* cnt;
+    int cap;
+    __device__ bool on(const DevGraph&) const { return true; }
+    __device__ void add(const DevGraph&, int v) const {
+        const int k = atomicAdd(cnt, 1);
+        if (k < cap) list[k] = v;
+    }
+};
+// v receives d > 0
+template <class Act>
+__device__ __forceinline__ void gain_e(const DevGraph& g, const Act& act, int v, int64_t d) {
+    if (act.on(g)) {
+        const int64_t old = add_e_old(g.e, v, d);
+        if (old <= 0 && old + d > 0) act.add(g, v);
+    } else {
+        add_e(g.e, v, d);
     }
 }
 __device__ __forceinline__ void add_bytes(const DevGraph& g, int cls, unsigned long long b) {
@@ -154,6 +181,57 @@ __device__ __forceinline__ long long wave_excl_scan64(long long x, long long* to
     const unsigned long long v = wave_incl_add((unsigned long long)x);
     *total = (long long)lane63(v);
     return (long long)v - x;
+}
+
+// The same over groups of G consecutive lanes (4, 8, 16 or the wave), for
+// rows that a group of lanes takes together.  Every lane of the wave calls
+// them.
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_move(unsigned long long x) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xF, 0xF, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xF, 0xF, false);
+    return ((unsigned long long)hi << 32) | lo;
+}
+template <int G>
+__device__ __forceinline__ unsigned long long group_min(unsigned long long x) {
+    if constexpr (G == WAVE) {
+        return wave_min_u64(x);
+    } else {
+        unsigned long long y;
+        y = dpp_move<0xB1>(x), x = y < x ? y : x;                            // the other lane of each pair
+        y = dpp_move<0x4E>(x), x = y < x ? y : x;                            // the other pair of the quad
+        if constexpr (G >= 8) y = dpp_move<0x141>(x), x = y < x ? y : x;     // the other quad of the eight
+        if constexpr (G >= 16) y = dpp_move<0x140>(x), x = y < x ? y : x;    // the other eight of the row
+        return x;
+    }
+}
+template <int G>
+__device__ __forceinline__ long long group_sum(long long x0) {
+    unsigned long long x = (unsigned long long)x0;
+    if constexpr (G == WAVE) {
+        return (long long)wave_sum_u64(x);
+    } else {
+        x += dpp_move<0xB1>(x);
+        x += dpp_move<0x4E>(x);
+        if constexpr (G >= 8) x += dpp_move<0x141>(x);
+        if constexpr (G >= 16) x += dpp_move<0x140>(x);
+        return (long long)x;
+    }
+}
+// exclusive prefix sum over the group (sub: the lane's place in it)
+template <int G>
+__device__ __forceinline__ long long group_excl_scan(long long x0, int sub) {
+    unsigned long long x = (unsigned long long)x0;
+    if constexpr (G == WAVE) {
+        x = wave_incl_add(x);
+    } else {
+        unsigned long long y;
+        y = dpp_move<0x111>(x), x += sub >= 1 ? y : 0ull;
+        y = dpp_move<0x112>(x), x += sub >= 2 ? y : 0ull;
+        if constexpr (G >= 8) y = dpp_move<0x114>(x), x += sub >= 4 ? y : 0ull;
+        if constexpr (G >= 16) y = dpp_move<0x118>(x), x += sub >= 8 ? y : 0ull;
+    }
+    return (long long)x - x0;
 }
 
 // Append one item per lane with pred set to list[*counter ...] using one
@@ -1752,8 +1830,8 @@ __device__ __forceinline__ int64_t amount(const DevGraph& g, int u) {
     return PULL ? -e : e;
 }
 
-template <bool PULL>
-__device__ __forceinline__ void do_push(DevGraph& g, int u, int j, int64_t eu) {
+template <bool PULL, class Act>
+__device__ __forceinline__ void do_push(DevGraph& g, const Act& act, int u, int j, int64_t eu) {
     int jo = PULL ? g.rev[j] : j;  // residual that shrinks
     int ji = PULL ? j : g.rev[j];  // residual that grows
     int32_t r = ld_res(g.cr, jo);
@@ -1764,20 +1842,20 @@ __device__ __forceinline__ void do_push(DevGraph& g, int u, int j, int64_t eu) {
     int w = g.cr[j].x;
     add_e(g.e, PULL ? w : u, -d);
     if (PULL) add_e(g.e, u, d);
-    else gain_e(g, w, d);
+    else gain_e(g, act, w, d);
 }
 
 // Move d along slot j of u without touching e(u) (the caller settles u's
 // excess once for all the moves of a cycle): the residual the move uses
 // shrinks, its reverse grows, and the neighbour's excess changes by d.
-template <bool PULL>
-__device__ __forceinline__ void move_along(DevGraph& g, int j, int32_t d) {
+template <bool PULL, class Act>
+__device__ __forceinline__ void move_along(DevGraph& g, const Act& act, int j, int32_t d) {
     int jo = PULL ? g.rev[j] : j;
     int ji = PULL ? j : g.rev[j];
     add_res(g.cr, jo, -d);
     add_res(g.cr, ji, d);
     if (PULL) add_e(g.e, g.cr[j].x, -(int64_t)d);
-    else gain_e(g, g.cr[j].x, d);
+    else gain_e(g, act, g.cr[j].x, d);
 }
 
 // Key of slot j for the lowest-neighbour search: (h(col) << 32 | j) when the
@@ -1789,32 +1867,35 @@ __device__ __forceinline__ unsigned long long ld_slot(const int2* cr, int j) {
 }
 
 // Scan slots [b + 0, b + STEP, ... b + (U-1)*STEP] (those below end) and fold
-// their keys into best.  All loads of the group are issued before any height
-// gather, so U slots are in flight per lane.
+// their keys into best; own: the row's vertex.  All loads of the group are
+// issued before any height gather, so U slots are in flight per lane: a load
+// under a branch would be waited for inside it, so a slot past the end reads
+// the last one, and a slot without residual gathers the row's own height.
 template <bool PULL, int U, int STEP>
-__device__ __forceinline__ void scan_group(const DevGraph& g, int b, int end, unsigned long long& best) {
+__device__ __forceinline__ void scan_group(const DevGraph& g, int own, int b, int end, unsigned long long& best) {
     unsigned long long sv[U];
     int32_t r[U];
 #pragma unroll
-    for (int q = 0; q < U; ++q) {
-        int j = b + q * STEP;
-        sv[q] = j < end ? ld_slot(g.cr, j) : 0ull;
+    for (int q = 0; q < U; ++q) sv[q] = ld_slot(g.cr, min(b + q * STEP, end - 1));
+    if (PULL) {
+        int rj[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) rj[q] = g.rev[min(b + q * STEP, end - 1)];
+#pragma unroll
+        for (int q = 0; q < U; ++q) r[q] = ld_res(g.cr, rj[q]);
     }
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-        int j = b + q * STEP;
-        r[q] = j < end ? (PULL ? ld_res(g.cr, g.rev[j]) : (int32_t)(sv[q] >> 32)) : 0;
+        if (!PULL) r[q] = (int32_t)(sv[q] >> 32);
+        if (b + q * STEP >= end) r[q] = 0;
     }
     unsigned hv[U];
 #pragma unroll
-    for (int q = 0; q < U; ++q) hv[q] = r[q] > 0 ? (unsigned)g.h[(int)(unsigned)sv[q]] : 0u;
+    for (int q = 0; q < U; ++q) hv[q] = (unsigned)g.h[r[q] > 0 ? (int)(unsigned)sv[q] : own];
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-        int j = b + q * STEP;
-        if (r[q] > 0) {
-            unsigned long long key = ((unsigned long long)hv[q] << 32) | (unsigned)j;
-            if (key < best) best = key;
-        }
+        const unsigned long long key = ((unsigned long long)hv[q] << 32) | (unsigned)(b + q * STEP);
+        if (r[q] > 0 && key < best) best = key;
     }
 }
 
@@ -1832,55 +1913,135 @@ constexpr int PR_UNROLL_BLOCK = 4;
 // still at that height, until the excess is gone: the cycles Algorithm 2
 // would spend saturating one lowest neighbour after another under the same
 // heights, done in one pass (heights only rise during push-relabel, so a
-// neighbour still at the scanned minimum is still admissible).  Thread: one lane owns u.  Wave: u is wave-uniform.  Block: u is
-// block-uniform and the whole block scans its row.
-template <bool PULL>
-__device__ __forceinline__ unsigned long long pr_thread_item(DevGraph& g, int u, int kc) {
+// neighbour still at the scanned minimum is still admissible).  Group: G
+// lanes own u.  Wave: u is wave-uniform.  Block: u is block-uniform and the
+// whole block scans its row.
+//
+// Rows of up to G * SL slots.  A row's time is its chain of trips to memory,
+// so the row is read once, SL slots per lane in flight at a time with their
+// reverse indices, and its residuals stay in registers: only u's own worker
+// lowers them, so an amount pushed against them is there (a residual that
+// grew meanwhile is seen by the next round).  A cycle is then the height
+// gather and the pushes.  The vertex is left when its excess is gone; what
+// arrives later puts it on the next worklist.  (A thread per row with a
+// reload per slot and a poll of e(u) for every cycle left took 39 us a launch
+// in a solve of RMAT-18, this 18.)  valid: whether this lane's group has a vertex; every lane of the
+// wave calls it.  *raised: h(u) went up.
+template <bool PULL, int G, int SL, class Act>
+__device__ __forceinline__ unsigned long long pr_group(const DevGraph& g, const Act& act, int u, bool valid, int kc,
+                                                       bool* raised) {
     const int N = g.n;
-    int beg = g.row_ptr[u];
-    int end = beg + g.row_len[u];
-    int hu = g.h[u];
-    unsigned long long bytes = 16;
-    for (int c = 0; c < kc && hu < N; ++c) {
-        int64_t eu = amount<PULL>(g, u);
-        if (eu <= 0) continue;
+    const int sub = lane_id() & (G - 1);
+    int beg = 0, len = 0, hu = N;
+    int64_t eu = 0;
+    if (valid) {
+        beg = g.row_ptr[u];
+        len = g.row_len[u];
+        hu = g.h[u];
+        eu = amount<PULL>(g, u);
+    }
+    int col[SL], rj[SL];
+    int32_t r[SL];
+    {
+        unsigned long long sv[SL];
+#pragma unroll
+        for (int k = 0; k < SL; ++k) {
+            const int j = beg + max(0, min(k * G + sub, len - 1));
+            sv[k] = ld_slot(g.cr, j);
+            rj[k] = g.rev[j];
+        }
+#pragma unroll
+        for (int k = 0; k < SL; ++k) {
+            const bool in = k * G + sub < len;
+            col[k] = (int)(unsigned)sv[k];
+            r[k] = (int32_t)(sv[k] >> 32);
+            if (PULL) r[k] = in ? ld_res(g.cr, rj[k]) : 0;
+            if (!in) r[k] = 0;
+        }
+    }
+    *raised = false;
+    unsigned long long bytes = valid && sub == 0 ? 16ull : 0ull;
+    int c = 0;
+    for (;;) {
+        const bool on = valid && c < kc && eu > 0 && hu < N;
+        if (!__any(on)) break;
+        int hv[SL];
+#pragma unroll
+        for (int k = 0; k < SL; ++k) hv[k] = g.h[on && r[k] > 0 ? col[k] : u];
         unsigned long long best = ~0ull;
-        for (int b = beg; b < end; b += PR_UNROLL) scan_group<PULL, PR_UNROLL, 1>(g, b, end, best);
-        bytes += 12ull * (unsigned long long)(end - beg);
-        if (best == ~0ull) {
-            hu = N;
-            g.h[u] = N;
-            mark_relabel(g, u);
-            break;
+#pragma unroll
+        for (int k = 0; k < SL; ++k) {
+            const unsigned long long key = ((unsigned long long)(unsigned)hv[k] << 32) | (unsigned)(k * G + sub);
+            if (r[k] > 0 && key < best) best = key;
         }
-        int bh = (int)(best >> 32);
-        int bj = (int)(unsigned)best;
-        if (hu <= bh) {
-            hu = bh + 1 < N ? bh + 1 : N;
-            g.h[u] = hu;
-            mark_relabel(g, u);
-            bytes += 4;
-            if (hu >= N || ++c >= kc) break;
+        best = group_min<G>(best);
+        const int bh = best == ~0ull ? N : (int)(best >> 32);
+        bool push = on;
+        if (on) {
+            if (sub == 0) bytes += 12ull * (unsigned long long)len;
+            if (hu <= bh) {  // (no residual slot: straight to |V|)
+                hu = bh + 1 < N ? bh + 1 : N;
+                *raised = true;
+                if (sub == 0) {
+                    g.h[u] = hu;
+                    mark_relabel(g, u);
+                    bytes += 4;
+                }
+                ++c;
+                push = hu < N && c < kc;
+            }
+            ++c;
         }
-        // push to bj, then to the following slots still at height bh, in
-        // slot order, until the excess is gone
-        int64_t left = eu;
-        for (int j = bj; j < end && left > 0; ++j) {
-            int32_t r = scan_res<PULL>(g, j);
-            if (r <= 0 || (j != bj && g.h[g.cr[j].x] != bh)) continue;
-            int32_t d = left < (int64_t)r ? (int32_t)left : r;
-            move_along<PULL>(g, j, d);
-            left -= d;
-            bytes += 48;
+        // to the lowest neighbours in slot order, until the excess is gone
+        int64_t left = push ? eu : 0;
+        int32_t d[SL];
+#pragma unroll
+        for (int k = 0; k < SL; ++k) {
+            const bool cand = push && r[k] > 0 && hv[k] == bh;
+            d[k] = 0;
+            if (!__any(cand)) continue;
+            const long long x = cand ? r[k] : 0;
+            const long long ex = group_excl_scan<G>(x, sub), tot = group_sum<G>(x);
+            if (cand && ex < left) d[k] = left - ex < (int64_t)r[k] ? (int32_t)(left - ex) : r[k];
+            left -= tot < left ? tot : left;
         }
-        if (left != eu) add_e(g.e, u, PULL ? eu - left : left - eu);
-        bytes += 12ull * (unsigned long long)(end - bj);
+        if (push && sub == 0) add_e(g.e, u, PULL ? eu - left : left - eu);
+        int64_t old[SL];
+#pragma unroll
+        for (int k = 0; k < SL; ++k) {
+            old[k] = 1;
+            if (d[k] > 0) {
+                const int j = beg + k * G + sub;
+                add_res(g.cr, PULL ? rj[k] : j, -d[k]);
+                add_res(g.cr, PULL ? j : rj[k], d[k]);
+                if (PULL) add_e(g.e, col[k], -(int64_t)d[k]);
+                else if (act.on(g)) old[k] = add_e_old(g.e, col[k], d[k]);
+                else add_e(g.e, col[k], d[k]);
+                r[k] -= d[k];
+                bytes += 48;
+            }
+        }
+        if (!PULL && act.on(g)) {
+#pragma unroll
+            for (int k = 0; k < SL; ++k)
+                if (old[k] <= 0 && old[k] + d[k] > 0) act.add(g, col[k]);
+        }
+        if (push) eu = left;
     }
     return bytes;
 }
 
-template <bool PULL>
-__device__ __forceinline__ unsigned long long pr_wave_item(DevGraph& g, int u, int kc) {
+// Lanes per short row, and slots per lane: rows of up to PR_G * PR_SL slots.
+// (Rows are binned by a tunable length: a longer one that lands in the short
+// bin is taken by its whole wave.)
+constexpr int PR_G = 4;
+constexpr int PR_SL = 4;
+// The same for rows a wave takes whole; longer ones are streamed.
+constexpr int PR_WSL = 4;
+
+template <bool PULL, class Act>
+__device__ __forceinline__ unsigned long long pr_wave_stream(DevGraph& g, const Act& act, int u, int kc,
+                                                             bool* raised) {
     const int N = g.n;
     const int lane = lane_id();
     int beg = bcast(g.row_ptr[u]);
@@ -1894,11 +2055,12 @@ __device__ __forceinline__ unsigned long long pr_wave_item(DevGraph& g, int u, i
         if (eu <= 0) continue;
         unsigned long long best = ~0ull;
         for (int b = beg; b < end; b += PR_UNROLL * WAVE)
-            scan_group<PULL, PR_UNROLL, WAVE>(g, b + lane, end, best);
+            scan_group<PULL, PR_UNROLL, WAVE>(g, u, b + lane, end, best);
         best = wave_min_u64(best);
         if (lane == 0) bytes += 12ull * (unsigned long long)(end - beg);
         if (best == ~0ull) {
             hu = N;
+            *raised = true;
             if (lane == 0) {
                 g.h[u] = N;
                 mark_relabel(g, u);
@@ -1909,6 +2071,7 @@ __device__ __forceinline__ unsigned long long pr_wave_item(DevGraph& g, int u, i
         int bj = (int)(unsigned)best;
         if (hu <= bh) {
             hu = bh + 1 < N ? bh + 1 : N;
+            *raised = true;
             if (lane == 0) {
                 g.h[u] = hu;
                 mark_relabel(g, u);
@@ -1928,7 +2091,7 @@ __device__ __forceinline__ unsigned long long pr_wave_item(DevGraph& g, int u, i
             long long ex = wave_excl_scan64(cand ? (long long)r : 0ll, &tot);
             if (cand && ex < left) {
                 int64_t room = left - ex;
-                move_along<PULL>(g, j, room < (int64_t)r ? (int32_t)room : r);
+                move_along<PULL>(g, act, j, room < (int64_t)r ? (int32_t)room : r);
                 bytes += 48;
             }
             left -= tot < left ? tot : left;
@@ -1939,8 +2102,33 @@ __device__ __forceinline__ unsigned long long pr_wave_item(DevGraph& g, int u, i
     return bytes;
 }
 
-template <bool PULL, int BS>
-__device__ __forceinline__ unsigned long long pr_block_item(DevGraph& g, int u, int kc) {
+// One row by a whole wave (u wave-uniform).
+template <bool PULL, class Act>
+__device__ __forceinline__ unsigned long long pr_wave_item(DevGraph& g, const Act& act, int u, int kc, bool* raised) {
+    *raised = false;
+    if (bcast(g.row_len[u]) <= WAVE * PR_WSL) return pr_group<PULL, WAVE, PR_WSL>(g, act, u, true, kc, raised);
+    return pr_wave_stream<PULL>(g, act, u, kc, raised);
+}
+
+// The short rows of a wave's lane groups (u where valid; every lane calls it).
+template <bool PULL, class Act>
+__device__ __forceinline__ unsigned long long pr_short_rows(DevGraph& g, const Act& act, int u, bool valid, int kc,
+                                                            bool* raised) {
+    const bool fits = valid && (g.bin0_max <= PR_G * PR_SL || g.row_len[u] <= PR_G * PR_SL);
+    unsigned long long bytes = pr_group<PULL, PR_G, PR_SL>(g, act, u, fits, kc, raised);
+    unsigned long long m = __ballot(valid && !fits && (lane_id() & (PR_G - 1)) == 0);
+    while (m) {  // wave-uniform
+        const int l = __ffsll((long long)m) - 1;
+        m &= m - 1;
+        bool up;
+        bytes += pr_wave_item<PULL>(g, act, __builtin_amdgcn_readlane(u, l), kc, &up);
+        if ((lane_id() & ~(PR_G - 1)) == l) *raised = up;
+    }
+    return bytes;
+}
+
+template <bool PULL, int BS, class Act>
+__device__ __forceinline__ unsigned long long pr_block_item(DevGraph& g, const Act& act, int u, int kc) {
     // Long rows: one pass per cycle.  While it looks for the lowest
     // neighbour, the pass already pushes to every residual slot whose
     // neighbour is at h(u) - 1 -- under a valid labelling the lowest height a
@@ -1974,12 +2162,10 @@ __device__ __forceinline__ unsigned long long pr_block_item(DevGraph& g, int u, 
         bool done = false;
         for (int b0 = beg; b0 < end && !done; b0 += PR_UNROLL_BLOCK * BS) {
             const int b = b0 + threadIdx.x;
+            // (no load under a branch, where it would be waited for: see scan_group)
             unsigned long long sv[PR_UNROLL_BLOCK];
 #pragma unroll
-            for (int q = 0; q < PR_UNROLL_BLOCK; ++q) {
-                int j = b + q * BS;
-                sv[q] = j < end ? ld_slot(g.cr, j) : 0ull;
-            }
+            for (int q = 0; q < PR_UNROLL_BLOCK; ++q) sv[q] = ld_slot(g.cr, min(b + q * BS, end - 1));
             int32_t r[PR_UNROLL_BLOCK];
 #pragma unroll
             for (int q = 0; q < PR_UNROLL_BLOCK; ++q) {
@@ -1988,7 +2174,7 @@ __device__ __forceinline__ unsigned long long pr_block_item(DevGraph& g, int u, 
             }
             unsigned hv[PR_UNROLL_BLOCK];
 #pragma unroll
-            for (int q = 0; q < PR_UNROLL_BLOCK; ++q) hv[q] = r[q] > 0 ? (unsigned)g.h[(int)(unsigned)sv[q]] : 0u;
+            for (int q = 0; q < PR_UNROLL_BLOCK; ++q) hv[q] = (unsigned)g.h[r[q] > 0 ? (int)(unsigned)sv[q] : u];
 #pragma unroll
             for (int q = 0; q < PR_UNROLL_BLOCK; ++q) {
                 const int j = b + q * BS;
@@ -2005,7 +2191,7 @@ __device__ __forceinline__ unsigned long long pr_block_item(DevGraph& g, int u, 
                 const int64_t before = (int64_t)bcast64((long long)base) + ex;
                 if (cand && before < eu) {
                     int64_t room = eu - before;
-                    move_along<PULL>(g, j, room < (int64_t)r[q] ? (int32_t)room : r[q]);
+                    move_along<PULL>(g, act, j, room < (int64_t)r[q] ? (int32_t)room : r[q]);
                     bytes += 48;
                 }
             }
@@ -2036,7 +2222,7 @@ __device__ __forceinline__ unsigned long long pr_block_item(DevGraph& g, int u, 
         if (bh < hu - 1) {
             // a neighbour below h(u) - 1 (heights moved meanwhile): push there
             if (threadIdx.x == 0) {
-                do_push<PULL>(g, u, bj, eu - moved);
+                do_push<PULL>(g, act, u, bj, eu - moved);
                 bytes += 48;
             }
         } else if (bh >= hu) {
@@ -2061,7 +2247,7 @@ __global__ void __launch_bounds__(BLOCK_PR, 8) k_pr_block(DevGraph g, const int3
     const int cnt = dcount ? *dcount : count;
     unsigned long long bytes = 0;
     for (int it = blockIdx.x; it < cnt; it += gridDim.x)  // whole blocks
-        bytes += pr_block_item<PULL, BLOCK_PR>(g, wl[it], kc);
+        bytes += pr_block_item<PULL, BLOCK_PR>(g, ActList{}, wl[it], kc);
     if (g.count_bytes) {
         const unsigned long long b = wave_sum_u64(bytes);
         if (lane_id() == 0 && b) add_bytes(g, KC_PR, b);
@@ -2071,8 +2257,8 @@ __global__ void __launch_bounds__(BLOCK_PR, 8) k_pr_block(DevGraph g, const int3
 // One launch for a round's thread and wave bins (the workgroup bin has its
 // own 1024-thread launch: in one kernel with these its registers would halve
 // their occupancy).  The 256-thread workgroups take virtual blocks in turn:
-// first BS / WAVE rows of the wave bin per block, then BS rows of the thread
-// bin.  Bin sizes: dcount[0..1] on the device when dcount is set, else c0, c1.
+// first BS / WAVE rows of the wave bin per block, then BS / PR_G rows of the
+// thread bin.  Bin sizes: dcount[0..1] on the device when dcount is set, else c0, c1.
 struct BinSizes {
     int c0, c1, c2;
 };
@@ -2089,18 +2275,20 @@ __global__ void __launch_bounds__(PR_SMALL_BLOCK) k_pr_small(DevGraph g, const i
     if (halted(g)) return;
     constexpr int BS = PR_SMALL_BLOCK, WPB = BS / WAVE;
     const BinSizes c = bin_sizes(dcount, c0, c1, 0);
-    const int nb1 = (c.c1 + WPB - 1) / WPB, nb0 = (c.c0 + BS - 1) / BS;
+    constexpr int RPB = BS / PR_G;  // short rows per block
+    const int nb1 = (c.c1 + WPB - 1) / WPB, nb0 = (c.c0 + RPB - 1) / RPB;
     const int total = nb1 + nb0;
-    unsigned long long bytes = 0;  // thread items per thread, wave items on lane 0
+    unsigned long long bytes = 0;
+    bool raised;
     for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {  // block-uniform roles
         if (vb < nb1) {
             const int w = vb * WPB + (int)threadIdx.x / WAVE;
             if (w < c.c1) {  // whole waves
-                bytes += pr_wave_item<PULL>(g, bcast(wl1[w]), kc);
+                bytes += pr_wave_item<PULL>(g, ActList{}, bcast(wl1[w]), kc, &raised);
             }
         } else {
-            const int i = (vb - nb1) * BS + (int)threadIdx.x;
-            if (i < c.c0) bytes += pr_thread_item<PULL>(g, wl0[i], kc);
+            const int i = (vb - nb1) * RPB + (int)threadIdx.x / PR_G;
+            bytes += pr_short_rows<PULL>(g, ActList{}, i < c.c0 ? wl0[i] : 0, i < c.c0, kc, &raised);
         }
     }
     if (g.count_bytes) {
@@ -2119,8 +2307,8 @@ __global__ void __launch_bounds__(PR_SMALL_BLOCK) k_pr_small(DevGraph g, const i
 // slot loads per lane are issued before their height gathers.
 constexpr int RIE_UNROLL = 4;
 
-template <int GROUP>
-__device__ __forceinline__ long long rie_item(DevGraph& g, int u, int sub, unsigned long long* bytes) {
+template <int GROUP, class Act>
+__device__ __forceinline__ long long rie_item(DevGraph& g, const Act& act, int u, int sub, unsigned long long* bytes) {
     int beg = g.row_ptr[u];
     int end = beg + g.row_len[u];
     int hu = g.h[u];
@@ -2128,22 +2316,21 @@ __device__ __forceinline__ long long rie_item(DevGraph& g, int u, int sub, unsig
     for (int j0 = beg + sub; j0 < end; j0 += GROUP * RIE_UNROLL) {
         unsigned long long sv[RIE_UNROLL];
 #pragma unroll
-        for (int q = 0; q < RIE_UNROLL; ++q) {
-            int j = j0 + q * GROUP;
-            sv[q] = j < end ? ld_slot(g.cr, j) : 0ull;
-        }
+        for (int q = 0; q < RIE_UNROLL; ++q) sv[q] = ld_slot(g.cr, min(j0 + q * GROUP, end - 1));
         int hv[RIE_UNROLL];
 #pragma unroll
-        for (int q = 0; q < RIE_UNROLL; ++q)
-            hv[q] = (int32_t)(sv[q] >> 32) > 0 ? g.h[(int)(unsigned)sv[q]] : INT_MAX;
+        for (int q = 0; q < RIE_UNROLL; ++q) {
+            const bool in = j0 + q * GROUP < end && (int32_t)(sv[q] >> 32) > 0;
+            hv[q] = g.h[in ? (int)(unsigned)sv[q] : u];  // u itself: never below u
+        }
 #pragma unroll
         for (int q = 0; q < RIE_UNROLL; ++q) {
-            if (hv[q] == INT_MAX || hu <= hv[q] + 1) continue;
+            if (hu <= hv[q] + 1) continue;
             int j = j0 + q * GROUP;
             int32_t x = xchg_res(g.cr, j, 0);
             if (x > 0) {
                 add_res(g.cr, g.rev[j], x);
-                gain_e(g, (int)(unsigned)sv[q], x);
+                gain_e(g, act, (int)(unsigned)sv[q], x);
                 moved += x;
                 *bytes += 32;
             }
@@ -2153,6 +2340,71 @@ __device__ __forceinline__ long long rie_item(DevGraph& g, int u, int sub, unsig
     return moved;
 }
 
+// The same for rows of up to G * SL slots taken by groups of G lanes, all
+// slots in flight at once (see pr_group); settles e(u).
+template <int G, int SL, class Act>
+__device__ __forceinline__ unsigned long long rie_group(const DevGraph& g, const Act& act, int u, bool valid) {
+    const int sub = lane_id() & (G - 1);
+    int beg = 0, len = 0, hu = 0;
+    if (valid) {
+        beg = g.row_ptr[u];
+        len = g.row_len[u];
+        hu = g.h[u];
+    }
+    unsigned long long sv[SL], bytes = valid && sub == 0 ? 16ull + 12ull * (unsigned long long)len : 0ull;
+    int rj[SL], hv[SL];
+#pragma unroll
+    for (int k = 0; k < SL; ++k) {
+        const int j = beg + max(0, min(k * G + sub, len - 1));
+        sv[k] = ld_slot(g.cr, j);
+        rj[k] = g.rev[j];
+    }
+#pragma unroll
+    for (int k = 0; k < SL; ++k) {
+        const bool in = k * G + sub < len && (int32_t)(sv[k] >> 32) > 0;
+        hv[k] = g.h[in ? (int)(unsigned)sv[k] : u];  // u itself: never below u
+    }
+    long long moved = 0;
+#pragma unroll
+    for (int k = 0; k < SL; ++k) {
+        if (!valid || hu <= hv[k] + 1) continue;
+        const int32_t x = xchg_res(g.cr, beg + k * G + sub, 0);
+        if (x > 0) {
+            const int v = (int)(unsigned)sv[k];
+            add_res(g.cr, rj[k], x);
+            gain_e(g, act, v, x);
+            moved += x;
+            bytes += 32;
+        }
+    }
+    if (__any(moved > 0)) {
+        moved = group_sum<G>(moved);
+        if (sub == 0 && moved) add_e(g.e, u, -moved);
+    }
+    return bytes;
+}
+
+template <class Act>
+__device__ __forceinline__ unsigned long long rie_wave_item(DevGraph& g, const Act& act, int u) {
+    if (bcast(g.row_len[u]) <= WAVE * PR_WSL) return rie_group<WAVE, PR_WSL>(g, act, u, true);
+    unsigned long long bytes = 0;
+    const long long moved = wave_sum_i64(rie_item<WAVE>(g, act, u, lane_id(), &bytes));
+    if (lane_id() == 0 && moved) add_e(g.e, u, -moved);
+    return bytes;
+}
+
+template <class Act>
+__device__ __forceinline__ unsigned long long rie_short_rows(DevGraph& g, const Act& act, int u, bool valid) {
+    const bool fits = valid && (g.bin0_max <= PR_G * PR_SL || g.row_len[u] <= PR_G * PR_SL);
+    unsigned long long bytes = rie_group<PR_G, PR_SL>(g, act, u, fits);
+    unsigned long long m = __ballot(valid && !fits && (lane_id() & (PR_G - 1)) == 0);
+    while (m) {  // wave-uniform
+        const int l = __ffsll((long long)m) - 1;
+        m &= m - 1;
+        bytes += rie_wave_item(g, act, __builtin_amdgcn_readlane(u, l));
+    }
+    return bytes;
+}
 
 // Remove-invalid-edges for a round's three bins in one launch (256-thread
 // workgroups taking virtual blocks as in k_pr_small, the workgroup bin's
@@ -2164,33 +2416,27 @@ __global__ void __launch_bounds__(256) k_rie_round(DevGraph g, const int32_t* wl
     constexpr int BS = 256, WPB = BS / WAVE;
     if (halted(g)) return;
     const BinSizes c = bin_sizes(dcount, c0, c1, c2);
-    const int nb2 = c.c2, nb1 = (c.c1 + WPB - 1) / WPB, nb0 = (c.c0 + BS - 1) / BS;
+    constexpr int RPB = BS / PR_G;  // short rows per block
+    const int nb2 = c.c2, nb1 = (c.c1 + WPB - 1) / WPB, nb0 = (c.c0 + RPB - 1) / RPB;
     const int total = nb2 + nb1 + nb0;
     unsigned long long bytes = 0;
     for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {  // block-uniform roles
         if (vb < nb2) {
             const int u = wl2[vb];
             if (g.relab && !bit_of(g.relab, u)) continue;  // block-uniform: h(u) kept, no invalid out-slot
-            const long long moved = wave_sum_i64(rie_item<BS>(g, u, (int)threadIdx.x, &bytes));
+            const long long moved = wave_sum_i64(rie_item<BS>(g, ActList{}, u, (int)threadIdx.x, &bytes));
             if (lane_id() == 0 && moved) add_e(g.e, u, -moved);
         } else if (vb < nb2 + nb1) {
             const int item = (vb - nb2) * WPB + (int)threadIdx.x / WAVE;
             if (item < c.c1) {  // whole waves
-                const int u = wl1[item];
-                if (!g.relab || bit_of(g.relab, u)) {
-                    const long long moved = wave_sum_i64(rie_item<WAVE>(g, u, lane_id(), &bytes));
-                    if (lane_id() == 0 && moved) add_e(g.e, u, -moved);
-                }
+                const int u = bcast(wl1[item]);
+                if (!g.relab || bit_of(g.relab, u)) bytes += rie_wave_item(g, ActList{}, u);
             }
         } else {
-            const int i = (vb - nb2 - nb1) * BS + (int)threadIdx.x;
-            if (i < c.c0) {
-                const int u = wl0[i];
-                if (!g.relab || bit_of(g.relab, u)) {
-                    const long long moved = rie_item<1>(g, u, 0, &bytes);
-                    if (moved) add_e(g.e, u, -moved);
-                }
-            }
+            const int i = (vb - nb2 - nb1) * RPB + (int)threadIdx.x / PR_G;
+            const int u = i < c.c0 ? wl0[i] : 0;
+            const bool valid = i < c.c0 && (!g.relab || bit_of(g.relab, u));
+            if (__any(valid)) bytes += rie_short_rows(g, ActList{}, u, valid);
         }
     }
     if (g.count_bytes) {
@@ -2551,9 +2797,14 @@ __device__ void solve_graph(GraphSlot& S, int mode, const GrTune& tune) {
         if (rounds_left > 0) --rounds_left;
         // push-relabel (Algorithm 2) over the three degree bins
         unsigned long long pb = 0;  // algorithmic bytes (counted while profiling)
-        for (int i = tid; i < c0; i += BS) pb += pr_thread_item<false>(g, S.wl0[i], S.kc);
-        for (int i = tid / WAVE; i < c1; i += BS / WAVE) pb += pr_wave_item<false>(g, bcast(S.wl1[i]), S.kc);
-        for (int i = 0; i < c2; ++i) pb += pr_block_item<false, BS>(g, S.wl2[i], S.kc_long);
+        bool raised;
+        for (int i0 = 0; i0 < c0; i0 += BS / PR_G) {
+            const int i = i0 + tid / PR_G;
+            pb += pr_short_rows<false>(g, ActNone{}, i < c0 ? S.wl0[i] : 0, i < c0, S.kc, &raised);
+        }
+        for (int i = tid / WAVE; i < c1; i += BS / WAVE)
+            pb += pr_wave_item<false>(g, ActNone{}, bcast(S.wl1[i]), S.kc, &raised);
+        for (int i = 0; i < c2; ++i) pb += pr_block_item<false, BS>(g, ActNone{}, S.wl2[i], S.kc_long);
         if (g.count_bytes) {
             const unsigned long long b = wave_sum_u64(pb);
             if (lane == 0 && b) add_bytes(g, KC_PR, b);
@@ -2561,19 +2812,14 @@ __device__ void solve_graph(GraphSlot& S, int mode, const GrTune& tune) {
         __syncthreads();
         // remove invalid edges (Algorithm 3)
         unsigned long long nb = 0;
-        for (int i = tid; i < c0; i += BS) {
-            int u = S.wl0[i];
-            long long moved = rie_item<1>(g, u, 0, &nb);
-            if (moved) add_e(g.e, u, -moved);
+        for (int i0 = 0; i0 < c0; i0 += BS / PR_G) {
+            const int i = i0 + tid / PR_G;
+            nb += rie_short_rows(g, ActNone{}, i < c0 ? S.wl0[i] : 0, i < c0);
         }
-        for (int i = tid / WAVE; i < c1; i += BS / WAVE) {
-            int u = bcast(S.wl1[i]);
-            long long moved = wave_sum_i64(rie_item<WAVE>(g, u, lane, &nb));
-            if (lane == 0 && moved) add_e(g.e, u, -moved);
-        }
+        for (int i = tid / WAVE; i < c1; i += BS / WAVE) nb += rie_wave_item(g, ActNone{}, bcast(S.wl1[i]));
         for (int i = 0; i < c2; ++i) {
             int u = S.wl2[i];
-            long long moved = wave_sum_i64(rie_item<BS>(g, u, tid, &nb));
+            long long moved = wave_sum_i64(rie_item<BS>(g, ActNone{}, u, tid, &nb));
             if (lane == 0 && moved) add_e(g.e, u, -moved);
         }
         if (g.count_bytes) {
@@ -2918,97 +3164,181 @@ __global__ void __launch_bounds__(256) k_value_if_empty(DevGraph g, DevCounters*
 // the rounds cost more in launches and host round trips than in work.  Here
 // one 1024-thread workgroup runs round after round with workgroup barriers
 // only: push-relabel over the list (Algorithm 2), remove-invalid-edges over
-// the same rows (Algorithm 3), then the next list from this one plus the
-// round's activations, each vertex once (mark == epoch), binned by row
-// length.  It stops after max_rounds rounds, or before a round whose list is
-// empty, longer than `limit` vertices or holds a workgroup-bin row (the
-// multi-block kernels take those).  Lists alternate between set a and set b
-// (input in a, counts in ctr->wl); on exit ctr->wl holds the counts of the
-// list to run next, ctr->rn_set which set holds it (0 a, 1 b) and
-// ctr->rn_rounds the rounds run.  Activations of the last round are already
-// in that list (the caller clears the activation count).
+// the rows it raised (Algorithm 3; the labelling is valid before every round,
+// so no other row can own a steep slot), then the next list from this one
+// plus the round's activations, each vertex once, binned by row length.  It
+// stops after max_rounds rounds, or before a round whose list is empty,
+// longer than `limit` (at most RN_MAX) vertices or holds a workgroup-bin row
+// (the multi-block kernels take those).
+//
+// A round is bound by its chain of trips to memory and by the barriers that
+// must see the pushes done; the lists, the activations and (LBM) the bit per
+// vertex that keeps a list free of repeats stay in LDS, and only the state of
+// the graph is in memory.  Measured on a 256 x 256 grid: 12 us a round before
+// (lists and repeat marks in memory, a thread per row, every row checked for
+// steep slots), 7.5 now.  Without LBM (more vertices than bits in LDS) the
+// repeats are found with mark[v] == epoch.
+//
+// Lists alternate between the two halves; input in a0, a1 with counts in
+// ctr->wl; on exit the list to run next is in set a, its counts in ctr->wl,
+// ctr->rn_set 0 and ctr->rn_rounds the rounds run.  Activations of the last
+// round are already in that list (the caller clears the activation count).
 constexpr int RN_BLOCK = 1024;
+constexpr int RN_MAX = 4096;     // vertices of a list
+constexpr int RN_STATIC = 512;   // the kernel's other LDS
+constexpr int RN_LISTS = 3 * RN_MAX * 4 + RN_MAX / 8;  // two lists, activations, raised flags
 
+template <bool LBM>
 __global__ void __launch_bounds__(RN_BLOCK) k_rounds_narrow(DevGraph g, int32_t* a0, int32_t* a1, int32_t* a2,
-                                                           int32_t* b0, int32_t* b1, int32_t* b2, int32_t* mark,
-                                                           int32_t* epoch, DevCounters* ctr, int kc, int max_rounds,
-                                                           int limit) {
+                                                           int32_t* mark, int32_t* epoch, DevCounters* ctr, int kc,
+                                                           int max_rounds, int limit) {
     if (halted(g)) return;
     constexpr int BS = RN_BLOCK;
-    __shared__ int s_c[3];
-    __shared__ int s_n[3];
-    __shared__ int s_ep;
-    __shared__ int s_na;
-    __shared__ int s_act;  // the round's activations: counted in LDS (one workgroup)
-    const int tid = threadIdx.x;
-    const int lane = lane_id();
-    DevGraph gl = g;
-    gl.act_cnt = &s_act;
-    if (tid < 3) s_c[tid] = ctr->wl[tid];
-    if (tid == 0) s_ep = *epoch;  // moved on here once per round, stored back at the end
+    extern __shared__ unsigned s_dyn[];
+    int* const lists = reinterpret_cast<int*>(s_dyn);   // each: short rows from the front, wave rows from the back
+    int* const acts = lists + 2 * RN_MAX;
+    unsigned* const s_up = s_dyn + 3 * RN_MAX;           // raised this round, by place in the list
+    unsigned* const s_in = s_up + RN_MAX / 32;           // LBM: in the next list, by vertex
+    __shared__ int s_c[2][3];
+    __shared__ int s_act;
+    __shared__ int s_any;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int words = (g.n + 31) >> 5;
+    int c0 = ctr->wl[0], c1 = ctr->wl[1], c2 = ctr->wl[2];
+    int ep = *epoch;
+    if (c2 != 0 || c0 + c1 == 0 || c0 + c1 > limit || max_rounds <= 0) {
+        if (tid == 0) {
+            ctr->rn_set = 0;
+            ctr->rn_rounds = 0;
+        }
+        return;
+    }
+    for (int i = tid; i < c0; i += BS) lists[i] = a0[i];
+    for (int i = tid; i < c1; i += BS) lists[RN_MAX - 1 - i] = a1[i];
+    if (LBM)
+        for (int i = tid; i < words; i += BS) s_in[i] = 0u;
+    if (tid < 3) s_c[1][tid] = 0;
+    for (int i = tid; i < RN_MAX / 32; i += BS) s_up[i] = 0u;
+    if (tid == 0) s_act = s_any = 0;
     __syncthreads();
-    int set = 0, r = 0;
-    for (; r < max_rounds; ++r) {
-        const int c0 = s_c[0], c1 = s_c[1], c2 = s_c[2];
-        if (c2 != 0 || c0 + c1 == 0 || c0 + c1 > limit) break;
-        const int32_t* in0 = set ? b0 : a0;
-        const int32_t* in1 = set ? b1 : a1;
-        int32_t* out[3] = {set ? a0 : b0, set ? a1 : b1, set ? a2 : b2};
-        if (tid == 0) s_act = 0;
-        __syncthreads();
-        // push-relabel (Algorithm 2): one thread per short row, one wave per longer row
-        for (int i = tid; i < c0; i += BS) pr_thread_item<false>(gl, in0[i], kc);
-        for (int w = tid / WAVE; w < c1; w += BS / WAVE) pr_wave_item<false>(gl, bcast(in1[w]), kc);
-        __syncthreads();
-        // remove invalid edges (Algorithm 3) over the same rows
-        unsigned long long nb = 0;
-        for (int i = tid; i < c0; i += BS) {
-            const int u = in0[i];
-            const long long moved = rie_item<1>(gl, u, 0, &nb);
-            if (moved) add_e(g.e, u, -moved);
+    DevGraph gl = g;
+    gl.relab = nullptr;  // raised rows are flagged in s_up
+    const ActLds act{acts, &s_act, RN_MAX};
+    int r = 0, half = 0;
+    bool full = false;  // the next list did not fit: it is in memory
+    for (;;) {
+        const int* in = lists + half * RN_MAX;
+        int* out = lists + (half ^ 1) * RN_MAX;
+        int* cnt = s_c[half ^ 1];
+        // push-relabel (Algorithm 2): a group of lanes per short row, a wave per longer row
+        for (int i0 = 0; i0 < c0; i0 += BS / PR_G) {
+            const int i = i0 + tid / PR_G;
+            bool raised;
+            pr_short_rows<false>(gl, act, i < c0 ? in[i] : 0, i < c0, kc, &raised);
+            if (raised && (lane & (PR_G - 1)) == 0) {
+                atomicOr(&s_up[i >> 5], 1u << (i & 31));
+                s_any = 1;
+            }
         }
         for (int w = tid / WAVE; w < c1; w += BS / WAVE) {
-            const int u = bcast(in1[w]);
-            const long long moved = wave_sum_i64(rie_item<WAVE>(gl, u, lane, &nb));
-            if (lane == 0 && moved) add_e(g.e, u, -moved);
-        }
-        // every wave's activations are counted before the count is read
-        __syncthreads();
-        if (tid == 0) {
-            ++s_ep;
-            s_na = s_act;
-        }
-        if (tid < 3) s_n[tid] = 0;
-        __syncthreads();
-        // the next list: this one and the round's activations, still active,
-        // each once; every vertex when activations overflowed the list
-        const int ep = s_ep;
-        const bool all = s_na > g.act_cap;
-        const long long total = all ? (long long)g.n : (long long)c0 + c1 + s_na;
-        for (long long i = tid; i < total; i += BS) {
-            int v;
-            if (all) v = (int)i;
-            else if (i < c0) v = in0[i];
-            else if (i < (long long)c0 + c1) v = in1[i - c0];
-            else v = g.act[i - c0 - c1];
-            if (v != g.s && v != g.t && v != g.pinned && ld_e(g.e, v) > 0 && g.h[v] < g.n &&
-                atomicExch(&mark[v], ep) != ep) {
-                const int len = g.row_len[v];
-                const int bin = len <= g.bin0_max ? 0 : (len <= g.bin1_max ? 1 : 2);
-                out[bin][atomicAdd(&s_n[bin], 1)] = v;
+            bool raised;
+            pr_wave_item<false>(gl, act, bcast(in[RN_MAX - 1 - w]), kc, &raised);
+            if (raised && lane == 0) {
+                const int i = RN_MAX - 1 - w;
+                atomicOr(&s_up[i >> 5], 1u << (i & 31));
+                s_any = 1;
             }
         }
         __syncthreads();
-        if (tid < 3) s_c[tid] = s_n[tid];
-        set ^= 1;
+        // remove invalid edges (Algorithm 3) over the raised rows
+        if (s_any) {
+            for (int i0 = 0; i0 < c0; i0 += BS / PR_G) {
+                const int i = i0 + tid / PR_G;
+                const bool up = i < c0 && bit_of(s_up, i);
+                if (__any(up)) rie_short_rows(gl, act, up ? in[i] : 0, up);
+            }
+            for (int w = tid / WAVE; w < c1; w += BS / WAVE) {
+                const int i = RN_MAX - 1 - w;
+                if (bit_of(s_up, i)) rie_wave_item(gl, act, bcast(in[i]));
+            }
+            // every wave's activations are counted before the count is read
+            __syncthreads();
+            for (int i = tid; i < RN_MAX / 32; i += BS) s_up[i] = 0u;
+        }
+        // the next list: this one and the round's activations, still active,
+        // each once; every vertex when activations overflowed their list
+        const int na = s_act;
+        const bool all = na > RN_MAX;
+        const long long total = all ? (long long)g.n : (long long)c0 + c1 + na;
+        ++ep;
+        auto build = [&](bool to_memory) {
+            for (long long i = tid; i < total; i += BS) {
+                int v;
+                if (all) v = (int)i;
+                else if (i < c0) v = in[i];
+                else if (i < (long long)c0 + c1) v = in[RN_MAX - 1 - ((int)i - c0)];
+                else v = acts[i - c0 - c1];
+                const int64_t ev = ld_e(g.e, v);
+                const int hv = g.h[v], len = g.row_len[v];
+                if (v == g.s || v == g.t || v == g.pinned || ev <= 0 || hv >= g.n) continue;
+                if (LBM && !to_memory) {
+                    const unsigned bit = 1u << (v & 31);
+                    if (atomicOr(&s_in[v >> 5], bit) & bit) continue;
+                } else if (atomicExch(&mark[v], ep) == ep) {
+                    continue;
+                }
+                const int bin = len <= g.bin0_max ? 0 : (len <= g.bin1_max ? 1 : 2);
+                const int k = atomicAdd(&cnt[bin], 1);
+                if (to_memory) (bin == 0 ? a0 : bin == 1 ? a1 : a2)[k] = v;
+                else if (bin == 2) a2[k] = v;
+                else if (k < RN_MAX) out[bin == 0 ? k : RN_MAX - 1 - k] = v;
+            }
+        };
+        build(false);
         __syncthreads();
+        const int n0 = cnt[0], n1 = cnt[1], n2 = cnt[2];
+        if (n0 + n1 > RN_MAX) {
+            // more than the lists hold: once more, into memory
+            __syncthreads();
+            if (tid < 3) cnt[tid] = 0;
+            ++ep;
+            __syncthreads();
+            build(true);
+            __syncthreads();
+            full = true;
+        }
+        ++r;
+        half ^= 1;
+        if (n0 + n1 == 0 || n2 != 0 || n0 + n1 > limit || r >= max_rounds) {
+            c0 = n0;
+            c1 = n1;
+            c2 = n2;
+            break;
+        }
+        // ready for the next round: its counts, flags and repeat bits
+        if (tid < 3) s_c[half ^ 1][tid] = 0;
+        if (tid == 0) s_act = s_any = 0;
+        c0 = n0;
+        c1 = n1;
+        if (LBM) {
+            for (int i = tid; i < c0; i += BS) s_in[lists[half * RN_MAX + i] >> 5] = 0u;
+            for (int i = tid; i < c1; i += BS) s_in[lists[half * RN_MAX + RN_MAX - 1 - i] >> 5] = 0u;
+        }
+        lds_barrier();
     }
-    if (tid < 3) ctr->wl[tid] = s_c[tid];
+    if (!full) {
+        const int* in = lists + half * RN_MAX;
+        for (int i = tid; i < c0; i += BS) a0[i] = in[i];
+        for (int i = tid; i < c1; i += BS) a1[i] = in[RN_MAX - 1 - i];
+    }
     if (tid == 0) {
-        ctr->wl[3] = s_c[0] + s_c[1] + s_c[2];
-        ctr->rn_set = set;
+        ctr->wl[0] = c0;
+        ctr->wl[1] = c1;
+        ctr->wl[2] = c2;
+        ctr->wl[3] = c0 + c1 + c2;
+        ctr->rn_set = 0;
         ctr->rn_rounds = r;
-        *epoch = s_ep;
+        *epoch = ep;
     }
 }
 
@@ -3401,7 +3731,7 @@ void launch_push_relabel_round(const DevGraph& g, const int32_t* const wl[3], co
         else k_pr_block<false><<<grid, BLOCK_PR, 0, st>>>(g, wl[2], cnt[2], kc_long, nullptr, d2);
     }
     const int64_t total = (int64_t)(cnt[1] + PR_SMALL_BLOCK / WAVE - 1) / (PR_SMALL_BLOCK / WAVE) +
-                          (cnt[0] + PR_SMALL_BLOCK - 1) / PR_SMALL_BLOCK;
+                          ((int64_t)cnt[0] * PR_G + PR_SMALL_BLOCK - 1) / PR_SMALL_BLOCK;
     if (total <= 0) return;
     const int grid = (int)std::min<int64_t>(total, dcount ? PR_SMALL_GRID : 1 << 30);
     if (pull) k_pr_small<true><<<grid, PR_SMALL_BLOCK, 0, st>>>(g, wl[0], wl[1], cnt[0], cnt[1], kc, dcount);
@@ -3410,7 +3740,7 @@ void launch_push_relabel_round(const DevGraph& g, const int32_t* const wl[3], co
 
 void launch_remove_invalid_round(const DevGraph& g, const int32_t* const wl[3], const int cnt[3], DevCounters* ctr,
                       hipStream_t st, const int32_t* dcount) {
-    const int64_t total = (int64_t)cnt[2] + (cnt[1] + 3) / 4 + (cnt[0] + 255) / 256;
+    const int64_t total = (int64_t)cnt[2] + (cnt[1] + 3) / 4 + ((int64_t)cnt[0] * PR_G + 255) / 256;
     if (total <= 0) return;
     const int grid = (int)std::min<int64_t>(total, dcount ? RIE_ROUND_GRID : 1 << 30);
     k_rie_round<<<grid, 256, 0, st>>>(g, wl[0], wl[1], wl[2], cnt[0], cnt[1], cnt[2], ctr, dcount);
@@ -3518,10 +3848,28 @@ void launch_round_terms_clear(DevCounters* ctr, hipStream_t st) {
     k_zero_counts<<<1, 64, 0, st>>>(ctr, 1, 0, nullptr);
 }
 
-void launch_rounds_narrow(const DevGraph& g, int32_t* const a[3], int32_t* const b[3], int32_t* mark,
-                          int32_t* epoch, DevCounters* ctr, int kc, int max_rounds, int limit, hipStream_t st) {
-    k_rounds_narrow<<<1, RN_BLOCK, 0, st>>>(g, a[0], a[1], a[2], b[0], b[1], b[2], mark, epoch, ctr, kc, max_rounds,
-                                           limit);
+int rounds_narrow_lds_bytes(int device) {
+    int max_lds = 0;
+    if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess) return 0;
+    const int bytes = max_lds - RN_STATIC;
+    if (bytes < RN_LISTS) return 0;
+    const void* fns[] = {reinterpret_cast<const void*>(&k_rounds_narrow<false>),
+                         reinterpret_cast<const void*>(&k_rounds_narrow<true>)};
+    for (const void* f : fns)
+        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return 0;
+    return bytes;
+}
+
+int rounds_narrow_max() { return RN_MAX; }
+
+void launch_rounds_narrow(const DevGraph& g, int32_t* const a[3], int32_t* mark, int32_t* epoch, DevCounters* ctr,
+                          int kc, int max_rounds, int limit, int lds_bytes, hipStream_t st) {
+    // the repeat bits in LDS where they fit beside the lists
+    const int bitmap = 4 * ((g.n + 31) / 32);
+    const bool lbm = RN_LISTS + bitmap <= lds_bytes;
+    auto fn = lbm ? k_rounds_narrow<true> : k_rounds_narrow<false>;
+    fn<<<1, RN_BLOCK, RN_LISTS + (lbm ? bitmap : 0), st>>>(g, a[0], a[1], a[2], mark, epoch, ctr, kc, max_rounds,
+                                                          std::min(limit, RN_MAX));
 }
 
 void launch_zero_act(DevCounters* ctr, hipStream_t st) {

@@ -362,12 +362,15 @@ void launch_set_i32(int32_t* p, int32_t value, hipStream_t st);
 void launch_halt_if_done(const DevCounters* ctr, int level_end, bool after_round, int32_t* halt, hipStream_t st);
 void launch_zero_act(DevCounters* ctr, hipStream_t st);
 // Up to max_rounds push-relabel + remove-invalid-edges rounds in one
-// workgroup while the worklist holds at most `limit` vertices and no
-// workgroup-bin row (input lists a with counts in ctr->wl; lists alternate
-// with b; ctr->wl, rn_set and rn_rounds say where it stopped).  dg.act must be
-// set, dg.relab null; epoch: the device epoch word (one per round).
-void launch_rounds_narrow(const DevGraph& g, int32_t* const a[3], int32_t* const b[3], int32_t* mark,
-                          int32_t* epoch, DevCounters* ctr, int kc, int max_rounds, int limit, hipStream_t st);
+// workgroup while the worklist holds at most `limit` vertices (and at most
+// rounds_narrow_max()) and no workgroup-bin row (lists a with counts in
+// ctr->wl, in place; rn_rounds says how many ran).  The labelling must be
+// valid.  epoch: the device epoch word (at most max_rounds + 1 more).
+void launch_rounds_narrow(const DevGraph& g, int32_t* const a[3], int32_t* mark, int32_t* epoch, DevCounters* ctr,
+                          int kc, int max_rounds, int limit, int lds_bytes, hipStream_t st);
+// dynamic LDS those launches may use on `device` (0: too little, never launch them)
+int rounds_narrow_lds_bytes(int device);
+int rounds_narrow_max();
 // the round value terms to zero (as a next-worklist build leaves them)
 void launch_round_terms_clear(DevCounters* ctr, hipStream_t st);
 // After a next-worklist build that found no active vertex (and, guard_level
