@@ -105,8 +105,8 @@ typedef struct mf_options {
                                   BFS is over (a relabel of depth d launches max(this, d + 1));
                                   <= 0: 7 */
     int32_t bfs_narrow_slots;  /* frontiers of at most this many slots run in one workgroup, many
-                                  levels per launch; 0: 4096, < 0: never; above what its LDS
-                                  holds (4096 to 8192 slots, by n): that */
+                                  levels per launch; 0: 4096, < 0: never; at most 8192 (what its
+                                  LDS holds) */
     int32_t bfs_medium_slots;  /* larger frontiers up to this many slots run in one cooperative
                                   launch of bfs_medium_blocks workgroups with a grid barrier per
                                   level; 0: 65536, < 0: never (also where cooperative launch is

@@ -452,9 +452,7 @@ void apply_loop_options(mf_graph* g, const mf_options& o) {
     auto on = [](int32_t v, bool dflt) { return v > 0 ? true : v < 0 ? false : dflt; };
     g->first_chunk = o.bfs_first_chunk > 0 ? o.bfs_first_chunk : 7;
     g->narrow_max = o.bfs_narrow_slots < 0 ? 0 : o.bfs_narrow_slots > 0 ? o.bfs_narrow_slots : 4096;
-    g->narrow_max = g->narrow_lds == 0
-                        ? 0
-                        : std::min<int64_t>(g->narrow_max, mf::narrow_map_slots(g->bits.nwords, g->narrow_lds));
+    if (g->narrow_lds == 0) g->narrow_max = 0;
     g->medium_max = o.bfs_medium_slots < 0 ? 0 : o.bfs_medium_slots > 0 ? o.bfs_medium_slots : 65536;
     g->medium_blocks = o.bfs_medium_blocks > 0 ? o.bfs_medium_blocks : 16;
     // mid-size frontiers need cooperative launch (every block resident)
@@ -617,13 +615,14 @@ mf_status global_relabel(mf_graph* g, const LoopMode& m, int64_t* levels_out, in
     // thin frontiers run in one workgroup, several levels per launch; the
     // first frontier is tried that way, later ones when a chunk leaves one
     // small enough
-    bool narrow = g->narrow_max > 0 && !g->trace_gr && (g->narrow_seed || !m.L.main);
+    const int64_t narrow_max = std::min<int64_t>(g->narrow_max, mf::narrow_limit(g->slot_cap));
+    bool narrow = narrow_max > 0 && !g->trace_gr && (g->narrow_seed || !m.L.main);
     bool medium = false;  // set when a read finds a mid-size frontier waiting
     const int64_t medium_cap = std::min<int64_t>(g->medium_max, m.L.mq.seg);
     const int medium_grid = std::min<int>(g->medium_blocks, m.L.mq_blocks);
     auto mid_size = [&](int lv) {
         const int64_t slots = (int64_t)(m.L.ctr_h->front[lv % 3] >> 32);
-        return medium_grid > 0 && m.L.mq.q && !g->coop_broken && !g->trace_gr && slots > g->narrow_max &&
+        return medium_grid > 0 && m.L.mq.q && !g->coop_broken && !g->trace_gr && slots > narrow_max &&
                slots <= medium_cap;
     };
     auto t_last = std::chrono::steady_clock::now();
@@ -637,7 +636,7 @@ mf_status global_relabel(mf_graph* g, const LoopMode& m, int64_t* levels_out, in
     for (;;) {
         if (narrow) {
             timed(g, m.L, mf::KC_GRS, [&] {
-                mf::launch_gr_narrow(m.dg, level, m.L.q[0], m.L.q[1], m.L.ctr, m.L.bits, g->narrow_max,
+                mf::launch_gr_narrow(m.dg, level, m.L.q[0], m.L.q[1], m.L.ctr, m.L.bits, narrow_max,
                                      g->narrow_lds, m.forward, st);
             });
             MF_HIP(hipGetLastError());
@@ -646,7 +645,7 @@ mf_status global_relabel(mf_graph* g, const LoopMode& m, int64_t* levels_out, in
             const int level_before = level;
             level = m.L.ctr_h->levels;
             if (level_before == 0 && main)
-                g->narrow_seed = (int64_t)(m.L.ctr_h->seed_front >> 32) <= g->narrow_max;
+                g->narrow_seed = (int64_t)(m.L.ctr_h->seed_front >> 32) <= narrow_max;
             const int cnt = (int)(unsigned)(m.L.ctr_h->front[level % 3] & 0xFFFFFFFFull);
             if (cnt == 0) break;
             if (level > g->n + 2) {
@@ -708,7 +707,7 @@ mf_status global_relabel(mf_graph* g, const LoopMode& m, int64_t* levels_out, in
         mf_status rc = read_lane(g, m.L);
         if (rc != MF_OK) return rc;
         // seeds of the next relabel: like this one's, as its level 0 recorded them
-        if (main) g->narrow_seed = (int64_t)(m.L.ctr_h->seed_front >> 32) <= g->narrow_max;
+        if (main) g->narrow_seed = (int64_t)(m.L.ctr_h->seed_front >> 32) <= narrow_max;
         const int cnt = (int)(unsigned)(m.L.ctr_h->front[level % 3] & 0xFFFFFFFFull);
         if (g->trace_gr) {
             // the level just done: its frontier, the unvisited slots before it,
@@ -735,7 +734,7 @@ mf_status global_relabel(mf_graph* g, const LoopMode& m, int64_t* levels_out, in
         }
         if (g->trace_gr) continue;  // one level per launch
         chunk = std::min(chunk * 2, 64);
-        narrow = g->narrow_max > 0 && (int64_t)(m.L.ctr_h->front[level % 3] >> 32) <= g->narrow_max;
+        narrow = narrow_max > 0 && (int64_t)(m.L.ctr_h->front[level % 3] >> 32) <= narrow_max;
         medium = !narrow && mid_size(level);
     }
     *levels_out += level;
@@ -1491,7 +1490,7 @@ mf_status ensure_lane2(mf_graph* g) {
         g->bits2.nwords = g->bits.nwords;
         if (dalloc(g, &g->wl2[0], n) != hipSuccess || dalloc(g, &g->wl2[1], n) != hipSuccess ||
             dalloc(g, &g->wl2[2], n) != hipSuccess ||
-            dalloc(g, &g->bits2.visited, 4 * (int64_t)g->bits2.nwords) != hipSuccess ||
+            dalloc(g, &g->bits2.visited, mf::GR_BITMAPS * (int64_t)g->bits2.nwords) != hipSuccess ||
             dalloc(g, &g->ctr2, 1) != hipSuccess || dalloc(g, &g->h2, n) != hipSuccess) {
             free_lane2(g);
             return MF_ERR_OUT_OF_MEMORY;
@@ -1687,9 +1686,9 @@ mf_status mf_graph_load(int32_t n, int64_t m, const int32_t* src, const int32_t*
         return fail(MF_ERR_OUT_OF_MEMORY);
     mf::launch_fill_i32(reinterpret_cast<int32_t*>(g->dg.bytes_part), 0,
                         2 * (int64_t)mf::KC_NCLASS * mf::BYTES_SLOTS, g->stream);
-    // BFS bitmaps: visited plus a ring of three frontier bitmaps
+    // BFS bitmaps: visited, a ring of three frontier bitmaps, the vertices with excess
     g->bits.nwords = (n + 31) / 32;
-    if (dalloc(g, &g->bits.visited, 4 * (int64_t)g->bits.nwords) != hipSuccess) return fail(MF_ERR_OUT_OF_MEMORY);
+    if (dalloc(g, &g->bits.visited, mf::GR_BITMAPS * (int64_t)g->bits.nwords) != hipSuccess) return fail(MF_ERR_OUT_OF_MEMORY);
     g->bits.fb = g->bits.visited + g->bits.nwords;
     {
         int coop = 0;
@@ -2088,7 +2087,7 @@ mf_status mf_graph_restore(mf_graph* g) {
         dalloc(g, &g->q[1], g->q_cap) || dalloc(g, &g->dg.e, n) || dalloc(g, &g->dg.h, n) ||
         dalloc(g, &g->wl[0], n) || dalloc(g, &g->wl[1], n) || dalloc(g, &g->wl[2], n) || dalloc(g, &g->need, n) ||
         dalloc(g, &g->side, n) || dalloc(g, &g->cut_acc, 8) ||
-        dalloc(g, &g->bits.visited, 4 * (int64_t)g->bits.nwords) ||
+        dalloc(g, &g->bits.visited, mf::GR_BITMAPS * (int64_t)g->bits.nwords) ||
         dalloc(g, &g->dg.bytes_part, (int64_t)mf::KC_NCLASS * mf::BYTES_SLOTS)) {
         free_device_state(g);
         return MF_ERR_OUT_OF_MEMORY;  // still offloaded, state intact on the host

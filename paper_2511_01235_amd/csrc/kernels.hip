@@ -534,7 +534,7 @@ __device__ __forceinline__ void gr_init_body(const Par& P, const DevGraph& g, in
     for (int base = P.bid * blockDim.x; base < N; base += P.nb * blockDim.x) {
         int v = base + threadIdx.x;
         int add = 0, slots = 0;
-        bool vis = false, front = false;
+        bool vis = false, front = false, exc = false;
         if (v < N && g.side && g.side[v] != g.side_keep) {
             g.h[v] = N;                 // the other side: never labelled by this relabel
             vis = true;
@@ -549,7 +549,8 @@ __device__ __forceinline__ void gr_init_body(const Par& P, const DevGraph& g, in
             if (cap_ok) {
                 const int ho = g.h[v];
                 g.h_prev[v] = ho;
-                if (other && ev > 0 && ho < N) excess++;
+                exc = other && ev > 0;
+                if (exc && ho < N) excess++;
                 if (other && ev < 0 && ho > 0) raised++;
             }
             g.h[v] = seed ? 0 : N;
@@ -561,7 +562,7 @@ __device__ __forceinline__ void gr_init_body(const Par& P, const DevGraph& g, in
             front = seed;
         }
         if (WORDS) {
-            const unsigned long long mv = __ballot(vis), mf = __ballot(front);
+            const unsigned long long mv = __ballot(vis), mf = __ballot(front), me = __ballot(exc);
             const int lane = lane_id();
             const int w = (v >> 5);
             if ((lane & 31) == 0 && w < bits.nwords) {
@@ -571,6 +572,7 @@ __device__ __forceinline__ void gr_init_body(const Par& P, const DevGraph& g, in
                 bits.fb[w] = hf;
                 bits.fb[(size_t)bits.nwords + w] = 0u;
                 bits.fb[2 * (size_t)bits.nwords + w] = 0u;
+                bits.fb[3 * (size_t)bits.nwords + w] = lane < 32 ? (unsigned)me : (unsigned)(me >> 32);
             }
         } else {
             if (vis) set_bit(bits.visited, v);
@@ -620,8 +622,11 @@ constexpr int GR_TD_U = 4;
 // its entries, and return its slot count for the direction counters.
 // A capped relabel counts the vertices with excess it labels (v gets height
 // lv + 1 here), per level.
-__device__ __forceinline__ void reached(const DevGraph& g, DevCounters* ctr, int lv, int v) {
-    if (g.bfs_cap && v != g.s && v != g.t && ld_e(g.e, v) > 0) atomicAdd(&ctr->bfs_disc[(lv + 1) % 3], 1);
+__device__ __forceinline__ bool has_excess(const GrBits& bits, int v) {
+    return bit_of(bits.fb + 3 * (size_t)bits.nwords, v);
+}
+__device__ __forceinline__ void reached(const DevGraph& g, const GrBits& bits, DevCounters* ctr, int lv, int v) {
+    if (g.bfs_cap && has_excess(bits, v)) atomicAdd(&ctr->bfs_disc[(lv + 1) % 3], 1);
 }
 
 // Whether a capped relabel stops before processing level lv: the vertices
@@ -650,7 +655,7 @@ __device__ __forceinline__ int discover(const DevGraph& g, DevCounters* ctr, con
                                         int* add) {
     set_bit(bits.visited, v);
     set_bit(bits.fb + (size_t)((lv + 1) % 3) * bits.nwords, v);
-    reached(g, ctr, lv, v);
+    reached(g, bits, ctr, lv, v);
     int len = g.row_len[v];
     *add = (len + GR_CHUNK - 1) / GR_CHUNK;
     return len;
@@ -743,7 +748,7 @@ __device__ __forceinline__ void gr_level_body(const Par& P, const DevGraph& g, i
             int add = 0, slots = 0;
             if (s_hit[tid]) {
                 g.h[v] = lv + 1;
-                reached(g, ctr, lv, v);
+                reached(g, bits, ctr, lv, v);
                 add = (len + GR_CHUNK - 1) / GR_CHUNK;
                 slots = len;
                 found++;
@@ -812,7 +817,7 @@ __device__ __forceinline__ void gr_level_body(const Par& P, const DevGraph& g, i
                 }
                 if (hit) {
                     g.h[v] = lv + 1;
-                    reached(g, ctr, lv, v);
+                    reached(g, bits, ctr, lv, v);
                     add = (len + GR_CHUNK - 1) / GR_CHUNK;
                     slots = len;
                     found++;
@@ -1029,130 +1034,199 @@ __device__ __forceinline__ void lds_barrier() {
 // relabel's stop, or at a level whose frontier is larger (not processed), and
 // leaves in ctr->levels the level to continue from.
 //
-// A level is bound by its chain of dependent accesses, not by bandwidth, so
-// everything a level hands to the next stays in LDS: `map` lists the slots of
-// the frontier's rows one by one (written by the lane that labels a vertex:
-// no queue entry to read, no prefix sum, no search), `list` its vertices,
-// and with LBM the visited bitmap is in LDS too (claimed there, no global
-// atomic).  What is left of the chain is a slot's {col, res, capsum} and then
-// the labelled vertex's row bounds and excess: two trips to memory a level.
-// Stores complete in half a microsecond and a wave's later loads count as
-// done only after its earlier stores, so the waves that scan store nothing:
-// the last waves of the workgroup write the heights of the vertices labelled
-// one level before, and the barrier between levels waits for LDS only.
-// Measured on a 256 x 256 grid: 6.8 us a level before (nine trips, five
-// barriers that drained stores), 2.3 now.
+// A level is bound by its chain of dependent accesses and by the instructions
+// on it, not by bandwidth, so everything a level hands to the next stays in
+// LDS: the frontier's rows as pieces of up to four slots, each scanned by
+// four lanes (the lane that labels a vertex writes its pieces: no queue entry
+// to read, no prefix sum, no search), and with LBM the visited bitmap,
+// claimed there instead of by a global atomic.  What is left of the chain is
+// a slot's {col, res, capsum} and then the labelled vertex's row bounds and
+// excess: two trips to memory a level.  Stores complete in half a microsecond
+// and a wave's later loads count as done only after its earlier stores, so
+// the waves that scan store nothing: the last waves of the workgroup write
+// the heights of the vertices labelled one level before, and the barrier
+// between levels waits for LDS only.  Measured on a 256 x 256 grid, per
+// level: 6.8 us with queue and counters in memory (nine trips, five barriers
+// that drained stores), 2.3 with a map of single slots in LDS, 1.8 with
+// pieces.
 //
-// LBM needs the bitmap beside maps and lists in LDS (the host checks);
-// without it the visited words are tested and claimed in global memory.  The
-// global queue is written at a hand-back only; the frontier bitmaps are not
-// kept up to date here (top-down needs only the visited bitmap): the host
-// rebuilds the current one before multi-block levels continue.
+// LBM needs the bitmap beside the pieces in LDS (the host checks).  Without
+// it a vertex is claimed by a CAS on its height after a test of its visited
+// word in memory, which the last waves set (neighbours share words: claiming
+// those serializes, 7.2 us a level on a 1024 x 1024 grid).  The global
+// queue is written at a hand-back only; the frontier bitmaps are not kept up
+// to date here (top-down needs only the visited bitmap): the host rebuilds
+// the current one before multi-block levels continue.
 constexpr int NARROW_BLOCK = 1024;
 constexpr int NARROW_SCAN = 768;         // threads that scan; the others write heights
-constexpr int NARROW_MAP = 8192;         // slots of a frontier at most
-constexpr int NARROW_MAP_MIN = 4096;     // ... and at least, with the bitmap beside the maps and lists
+constexpr int NP = 4;                    // slots of a piece, and lanes that scan it
+constexpr int NARROW_CAP = 4096;         // pieces of a frontier, at most
+constexpr int NARROW_CAP_MIN = 1536;     // ... with the bitmap in LDS, at least
+constexpr int NARROW_MAX = 8192;         // slots of a frontier
 constexpr int NARROW_STATIC = 128;       // the kernel's other LDS
-constexpr int NARROW_ROW = 32;           // longer rows are written to the map by their whole wave
+constexpr int64_t NARROW_SLOTS = 1ll << 29;  // graphs with more slots are not taken (a piece's first slot has 29 bits)
 
-// One level's {slots, vertices} in an LDS word, slots in the high half.
+// A piece: x its vertex, y its first slot << 3 | whether it starts the row << 2
+// | its slots - 1.
+__device__ __forceinline__ int2 narrow_piece(int v, int beg, int len, int i, bool whole) {
+    return make_int2(v, (int)((unsigned)(beg + NP * i) << 3 | (whole && i == 0 ? 4u : 0u) |
+                              (unsigned)(min(len - NP * i, NP) - 1)));
+}
+
+// What a level leaves for the next one: pieces, their count and the slots
+// they cover ({slots, pieces} in one word), the vertices with excess among
+// them, and queue entries of vertices whose pieces did not fit.
+struct NarrowOut {
+    int2* rec;
+    int cap;                     // pieces that fit
+    unsigned long long* front;
+    int* disc;
+    unsigned* spill;
+    int2* q;
+    int32_t* h;
+    unsigned* visited;           // null: kept in LDS
+    int height;
+};
+
 // Called by a whole wave: up to U vertices per lane (vs[k], slots beg[k] ..
-// beg[k] + len[k], none where len[k] is 0) go behind what *front counts.
-// (A frontier of more than cap slots is handed back from its list: its map
-// may be cut short.)
+// beg[k] + len[k], none where len[k] is 0).  whole: they are whole rows.
 template <int U>
-__device__ __forceinline__ void narrow_put(const int (&vs)[U], const int (&beg)[U], const int (&len)[U], int* map,
-                                           int* list, int cap, unsigned long long* front) {
-    unsigned sl = 0, cnt = 0;
+__device__ __forceinline__ void narrow_put(const int (&vs)[U], const int (&beg)[U], const int (&len)[U], bool whole,
+                                           const NarrowOut& o) {
+    int most = 0;
+    unsigned base = 0, cnt = 0;  // the wave's place and pieces
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-        sl += (unsigned)len[k];
-        cnt += len[k] > 0 ? 1u : 0u;
-    }
-    const unsigned icnt = wave_incl_add(cnt);
-    const unsigned tcnt = lane63(icnt);
-    if (tcnt == 0) return;  // wave-uniform
-    const unsigned isl = wave_incl_add(sl);
-    unsigned long long base = 0;
-    if (lane_id() == 0) base = atomicAdd(front, ((unsigned long long)lane63(isl) << 32) | tcnt);
-    base = (unsigned long long)bcast64((int64_t)base);
-    unsigned so = (unsigned)(base >> 32) + isl - sl;
-    unsigned at = (unsigned)base + icnt - cnt;
+    for (int k = 0; k < U; ++k) most = max(most, len[k]);
+    if (!__any(most > 0)) return;  // wave-uniform
+    if (!__any(most > NP)) {
+        // one piece per vertex: places and slots by ballots
+        unsigned long long m[U];
+        unsigned sl = 0;
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-        if (len[k] > 0) list[at++] = vs[k];
-        if (len[k] <= NARROW_ROW)
-            for (int i = 0; i < len[k]; ++i)
-                if (so + i < (unsigned)cap) map[so + i] = beg[k] + i;
-        unsigned long long lm = __ballot(len[k] > NARROW_ROW);
-        while (lm) {  // wave-uniform
-            const int l = __ffsll((long long)lm) - 1;
-            lm &= lm - 1;
-            const int b = __builtin_amdgcn_readlane(beg[k], l), n = __builtin_amdgcn_readlane(len[k], l);
-            const unsigned o = (unsigned)__builtin_amdgcn_readlane((int)so, l);
-            for (int i = lane_id(); i < n && o + i < (unsigned)cap; i += WAVE) map[o + i] = b + i;
+        for (int k = 0; k < U; ++k) {
+            m[k] = __ballot(len[k] > 0);
+            cnt += (unsigned)__popcll(m[k]);
+            sl += (unsigned)__popcll(__ballot(len[k] & 1)) + 2u * (unsigned)__popcll(__ballot(len[k] & 2)) +
+                  4u * (unsigned)__popcll(__ballot(len[k] & 4));
         }
-        so += (unsigned)len[k];
+        if (lane_id() == 0) base = (unsigned)atomicAdd(o.front, ((unsigned long long)sl << 32) | cnt);
+        base = (unsigned)bcast((int)base);
+        if (base + cnt <= (unsigned)o.cap) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const unsigned below = __builtin_amdgcn_mbcnt_hi((unsigned)(m[k] >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((unsigned)m[k], 0u));
+                if (len[k] > 0) o.rec[base + below] = narrow_piece(vs[k], beg[k], len[k], 0, whole);
+                base += (unsigned)__popcll(m[k]);
+            }
+            return;
+        }
+    } else {
+        unsigned mine = 0, sl = 0;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            mine += (unsigned)(len[k] + NP - 1) / NP;
+            sl += (unsigned)len[k];
+        }
+        const unsigned incl = wave_incl_add(mine), isl = wave_incl_add(sl);
+        cnt = lane63(incl);
+        if (lane_id() == 0) base = (unsigned)atomicAdd(o.front, ((unsigned long long)lane63(isl) << 32) | cnt);
+        base = (unsigned)bcast((int)base);
+        if ((unsigned long long)base + cnt <= (unsigned)o.cap) {
+            unsigned at = base + incl - mine;
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int n = (len[k] + NP - 1) / NP;
+                if (n <= 8)
+                    for (int i = 0; i < n; ++i) o.rec[at + i] = narrow_piece(vs[k], beg[k], len[k], i, whole);
+                unsigned long long lm = __ballot(n > 8);  // long rows by the whole wave
+                while (lm) {                              // wave-uniform
+                    const int l = __ffsll((long long)lm) - 1;
+                    lm &= lm - 1;
+                    const int v = __builtin_amdgcn_readlane(vs[k], l), b = __builtin_amdgcn_readlane(beg[k], l);
+                    const int n2 = __builtin_amdgcn_readlane(len[k], l);
+                    const unsigned a = (unsigned)__builtin_amdgcn_readlane((int)at, l);
+                    for (int i = lane_id(); NP * i < n2; i += WAVE) o.rec[a + i] = narrow_piece(v, b, n2, i, whole);
+                }
+                at += (unsigned)n;
+            }
+            return;
+        }
     }
+    // the pieces do not fit (the level will be handed back): straight to the
+    // global queue, with their heights, and no piece in the places counted
+    for (unsigned i = base + lane_id(); i < (unsigned)o.cap && i - base < cnt; i += WAVE) o.rec[i] = make_int2(0, 0);
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+        if (len[k] > 0) {
+            o.h[vs[k]] = o.height;
+            if (o.visited) set_bit(o.visited, vs[k]);
+            unsigned p = atomicAdd(o.spill, (unsigned)(len[k] + GR_CHUNK - 1) / GR_CHUNK);
+            for (int a = 0; a < len[k]; a += GR_CHUNK) o.q[p++] = make_int2(vs[k], a);
+        }
 }
 
 template <bool FWD, bool LBM, int U>
-__device__ __forceinline__ int narrow_slots(const DevGraph& g, const GrBits& bits, int fs, const int* map, int* next,
-                                            int* list, int cap, unsigned* s_vis, unsigned long long* front,
-                                            int* s_disc) {
-    const int tid = threadIdx.x;
+__device__ __forceinline__ int narrow_slots(const DevGraph& g, const GrBits& bits, int np, const int2* rec,
+                                            unsigned* s_vis, const NarrowOut& o) {
+    constexpr int PER = NARROW_SCAN / NP;  // pieces in one step
+    const int place = threadIdx.x / NP, sub = threadIdx.x % NP;
+    const int first = bcast(place);        // the wave's first piece
     int found = 0;
-    for (int base = 0; base < fs; base += U * NARROW_SCAN) {
+    for (int base = 0; base + first < np; base += U * PER) {
         int2 c[U];
         int32_t sum[U], r[U];
+        bool in[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) {  // every load of the U slots is issued before the first is used
-            const int j = map[min(base + k * NARROW_SCAN + tid, fs - 1)];
+            const int p = base + k * PER + place;
+            const int2 pc = rec[min(p, np - 1)];
+            in[k] = p < np && sub <= (pc.y & 3);
+            const unsigned j = ((unsigned)pc.y >> 3) + (in[k] ? sub : 0);
             c[k] = g.cr[j];
             sum[k] = FWD ? 0 : g.capsum[j];
         }
         bool won[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            r[k] = base + k * NARROW_SCAN + tid < fs ? (FWD ? c[k].y : sum[k] - c[k].y) : 0;
+            r[k] = in[k] ? (FWD ? c[k].y : sum[k] - c[k].y) : 0;
             // the pinned vertex and the other side are marked visited at init
-            const int v = c[k].x;
-            const unsigned bit = 1u << (v & 31);
-            if (LBM) won[k] = r[k] > 0 && !(atomicOr(&s_vis[v >> 5], bit) & bit);
-            else won[k] = r[k] > 0 && !bit_of(bits.visited, v);
+            won[k] = r[k] > 0 && !bit_of(LBM ? s_vis : bits.visited, c[k].x);
         }
-        if (!LBM) {
-            unsigned old[U];
-#pragma unroll
-            for (int k = 0; k < U; ++k) {
-                old[k] = ~0u;
-                if (won[k]) old[k] = atomicOr(&bits.visited[c[k].x >> 5], 1u << (c[k].x & 31));
-            }
-#pragma unroll
-            for (int k = 0; k < U; ++k) won[k] = won[k] && !(old[k] >> (c[k].x & 31) & 1u);
-        }
-        int vs[U], beg[U], len[U];
-        int64_t ex[U];
+        unsigned old[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
+            if (LBM) {
+                old[k] = ~0u;
+                if (won[k]) old[k] = atomicOr(&s_vis[c[k].x >> 5], 1u << (c[k].x & 31));
+            } else {
+                old[k] = 0u;
+                if (won[k]) old[k] = (unsigned)atomicCAS(&g.h[c[k].x], g.n, o.height);
+            }
+        }
+        int vs[U], beg[U], len[U];
+        unsigned ex[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            won[k] = LBM ? !(old[k] >> (c[k].x & 31) & 1u) : old[k] == (unsigned)g.n;
             vs[k] = c[k].x;
             beg[k] = 0;
             len[k] = 0;
-            ex[k] = 0;
+            ex[k] = 0u;
             if (won[k]) {
                 beg[k] = g.row_ptr[vs[k]];
                 len[k] = g.row_len[vs[k]];
-                if (g.bfs_cap) ex[k] = ld_e(g.e, vs[k]);
+                if (g.bfs_cap) ex[k] = bits.fb[3 * (size_t)bits.nwords + (vs[k] >> 5)];
             }
         }
-        narrow_put<U>(vs, beg, len, next, list, cap, front);
+        narrow_put<U>(vs, beg, len, true, o);
         int disc = 0;
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            disc += ex[k] > 0 && vs[k] != g.s && vs[k] != g.t;
+            disc += (int)__popcll(__ballot(ex[k] >> (vs[k] & 31) & 1u));
             found += won[k];
         }
-        if (disc) atomicAdd(s_disc, disc);
+        if (disc && lane_id() == 0) atomicAdd(o.disc, disc);
     }
     return found;
 }
@@ -1160,14 +1234,13 @@ __device__ __forceinline__ int narrow_slots(const DevGraph& g, const GrBits& bit
 template <bool FWD, bool LBM>
 __global__ void __launch_bounds__(NARROW_BLOCK) k_gr_narrow(DevGraph g, int lv0, int2* q0, int2* q1,
                                                             DevCounters* ctr, GrBits bits, long long max_slots,
-                                                            int map_cap) {
+                                                            int pieces) {
     extern __shared__ unsigned s_dyn[];
     __shared__ unsigned long long s_front[3];  // a ring by level
     __shared__ int s_disc[3];                  // vertices with excess labelled, by level
     __shared__ unsigned s_pieces;              // hand-back: queue entries
-    int* const maps = reinterpret_cast<int*>(s_dyn);
-    int* const lists = maps + 2 * map_cap;
-    unsigned* const s_vis = s_dyn + 4 * map_cap;
+    int2* const recs = reinterpret_cast<int2*>(s_dyn);
+    unsigned* const s_vis = s_dyn + 4 * pieces;
     const int tid = threadIdx.x;
     const bool cap = g.bfs_cap != 0;
     const unsigned long long front0 = ctr->front[lv0 % 3];
@@ -1175,9 +1248,9 @@ __global__ void __launch_bounds__(NARROW_BLOCK) k_gr_narrow(DevGraph g, int lv0,
     long long mu = ctr->unv[(lv0 + 2) % 3];  // unvisited slots, as the direction rule keeps them
     int lab = cap ? excess_labelled(ctr, lv0) : 0;
     const int total = cap ? excess_total(ctr) : INT_MAX;
-    if (max_slots > map_cap) max_slots = map_cap;
     if (tid == 0 && lv0 == 0) ctr->seed_front = front0;
-    if (cnt0 == 0 || (long long)(front0 >> 32) > max_slots) {
+    // (pieces: at most one short one per queue entry)
+    if (cnt0 == 0 || (long long)(front0 >> 32) > max_slots || (front0 >> 32) / NP + (unsigned)cnt0 > (unsigned)pieces) {
         if (tid == 0) ctr->levels = lv0;
         return;
     }
@@ -1189,8 +1262,10 @@ __global__ void __launch_bounds__(NARROW_BLOCK) k_gr_narrow(DevGraph g, int lv0,
     }
     if (tid == 0) s_pieces = 0;
     __syncthreads();
-    {   // the incoming frontier's slots (its heights are written)
+    {   // the incoming frontier (its heights are written)
         const int2* qin = (lv0 & 1) ? q1 : q0;
+        const NarrowOut o{recs + (lv0 & 1) * pieces, pieces, &s_front[0], &s_disc[0], &s_pieces, nullptr, g.h,
+                          nullptr, lv0};
         for (int k0 = 0; k0 < cnt0; k0 += NARROW_BLOCK) {
             int vs[1] = {0}, beg[1] = {0}, len[1] = {0};
             if (k0 + tid < cnt0) {
@@ -1199,59 +1274,63 @@ __global__ void __launch_bounds__(NARROW_BLOCK) k_gr_narrow(DevGraph g, int lv0,
                 beg[0] = g.row_ptr[ent.x] + ent.y;
                 len[0] = min(g.row_len[ent.x] - ent.y, GR_CHUNK);
             }
-            narrow_put<1>(vs, beg, len, maps + (lv0 & 1) * map_cap, lists + (lv0 & 1) * map_cap, map_cap,
-                          &s_front[lv0 % 3]);
+            narrow_put<1>(vs, beg, len, false, o);
         }
     }
     unsigned long long scanned = 0, found = 0, f = 0;
-    int lv = lv0, mode = 0;
+    int lv = lv0, mode = 0, cur = 0;  // cur: the level's place in the rings
     for (;;) {
-        lds_barrier();  // the level's map, list and counts are complete
-        f = s_front[lv % 3];
-        const int fs = (int)(f >> 32);
-        if (lv > lv0) lab += s_disc[lv % 3];
+        lds_barrier();  // the level's pieces and counts are complete
+        f = s_front[cur];
+        lab += s_disc[cur];  // (none counted for the incoming frontier)
+        const int np = __builtin_amdgcn_readfirstlane((int)(unsigned)f);
+        const int fs = __builtin_amdgcn_readfirstlane((int)(f >> 32));
         // 1: the BFS is over; 2: a capped relabel that has labelled every
         // vertex with excess; 3: a frontier with too many slots for here
-        if ((unsigned)f == 0) mode = 1;
+        if (np == 0) mode = 1;
         else if (lab >= total) mode = 2;
-        else if ((long long)(f >> 32) > max_slots || lv > g.n) mode = 3;
+        else if ((unsigned)fs > max_slots || (unsigned)np > (unsigned)pieces || lv > g.n) mode = 3;
         if (mode) break;
-        if (tid == 0) {  // (last read before the barrier above)
-            s_front[(lv + 2) % 3] = 0;
-            s_disc[(lv + 2) % 3] = 0;
+        const int nxt = cur == 2 ? 0 : cur + 1;
+        const int last = nxt == 2 ? 0 : nxt + 1;
+        if (tid == NARROW_BLOCK - 1) {  // (last read before the barrier above)
+            s_front[last] = 0;
+            s_disc[last] = 0;
         }
         mu -= fs;
-        const int* map = maps + (lv & 1) * map_cap;
+        const int2* rec = recs + (lv & 1) * pieces;
         if (tid >= NARROW_SCAN) {
-            if (lv > lv0) {
-                const int* in = lists + (lv & 1) * map_cap;
-                for (int i = tid - NARROW_SCAN; i < (int)(unsigned)f; i += NARROW_BLOCK - NARROW_SCAN) g.h[in[i]] = lv;
-            }
+            if (lv > lv0)
+                for (int i = tid - NARROW_SCAN; i < np; i += NARROW_BLOCK - NARROW_SCAN) {
+                    const int2 pc = rec[i];
+                    if (!(pc.y & 4)) continue;
+                    if (LBM) g.h[pc.x] = lv;
+                    else set_bit(bits.visited, pc.x);
+                }
         } else {
-            int* next = maps + ((lv + 1) & 1) * map_cap;
-            int* list = lists + ((lv + 1) & 1) * map_cap;
-            unsigned long long* nf = &s_front[(lv + 1) % 3];
-            int* nd = &s_disc[(lv + 1) % 3];
-            if (fs <= NARROW_SCAN)
-                found += narrow_slots<FWD, LBM, 1>(g, bits, fs, map, next, list, map_cap, s_vis, nf, nd);
-            else if (fs <= 2 * NARROW_SCAN)
-                found += narrow_slots<FWD, LBM, 2>(g, bits, fs, map, next, list, map_cap, s_vis, nf, nd);
-            else
-                found += narrow_slots<FWD, LBM, 4>(g, bits, fs, map, next, list, map_cap, s_vis, nf, nd);
+            const NarrowOut o{recs + ((lv + 1) & 1) * pieces, pieces, &s_front[nxt], &s_disc[nxt], &s_pieces,
+                              (lv & 1) ? q0 : q1, g.h, LBM ? nullptr : bits.visited, lv + 1};
+            if (np <= NARROW_SCAN / NP) found += narrow_slots<FWD, LBM, 1>(g, bits, np, rec, s_vis, o);
+            else if (np <= 2 * (NARROW_SCAN / NP)) found += narrow_slots<FWD, LBM, 2>(g, bits, np, rec, s_vis, o);
+            else found += narrow_slots<FWD, LBM, 4>(g, bits, np, rec, s_vis, o);
         }
         scanned += fs;
         ++lv;
+        cur = nxt;
     }
     if (lv > lv0) {  // the last level's heights, and its queue if it is handed back
-        const int* in = lists + (lv & 1) * map_cap;
+        const int2* rec = recs + (lv & 1) * pieces;
         int2* q = (lv & 1) ? q1 : q0;
-        for (int i = tid; i < (int)(unsigned)f; i += NARROW_BLOCK) {
-            const int v = in[i];
-            g.h[v] = lv;
+        const unsigned np = (unsigned)f;
+        for (unsigned i = tid; i < min(np, (unsigned)pieces); i += NARROW_BLOCK) {
+            const int2 pc = rec[i];
+            if (!(pc.y & 4)) continue;
+            if (LBM) g.h[pc.x] = lv;
+            else set_bit(bits.visited, pc.x);
             if (mode == 3) {
-                const int len = g.row_len[v];
+                const int len = g.row_len[pc.x];
                 unsigned p = atomicAdd(&s_pieces, (unsigned)(len + GR_CHUNK - 1) / GR_CHUNK);
-                for (int a = 0; a < len; a += GR_CHUNK) q[p++] = make_int2(v, a);
+                for (int a = 0; a < len; a += GR_CHUNK) q[p++] = make_int2(pc.x, a);
             }
         }
         if (LBM && mode == 3)
@@ -1596,7 +1675,7 @@ __global__ void __launch_bounds__(GRM_BLOCK) k_gr_medium(DevGraph g, int lv0, in
                         set_bit(bits.visited, v);
                         rp[k] = g.row_ptr[v];
                         rl[k] = g.row_len[v];
-                        ex[k] = cap && v != g.s && v != g.t && ld_e(g.e, v) > 0;
+                        ex[k] = cap && has_excess(bits, v);
                         found++;
                     }
                 }
@@ -3626,7 +3705,7 @@ int narrow_lds_bytes(int device) {
     int max_lds = 0;
     if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess) return 0;
     const int bytes = max_lds - NARROW_STATIC;
-    if (bytes < 16 * NARROW_MAP) return 0;
+    if (bytes < 16 * NARROW_CAP) return 0;
     const void* fns[] = {reinterpret_cast<const void*>(&k_gr_narrow<false, false>),
                          reinterpret_cast<const void*>(&k_gr_narrow<false, true>),
                          reinterpret_cast<const void*>(&k_gr_narrow<true, false>),
@@ -3636,22 +3715,18 @@ int narrow_lds_bytes(int device) {
     return bytes;
 }
 
-// slots that fit each of two maps and lists with the visited bitmap beside them in LDS
-static int narrow_room(int nwords, int lds_bytes) { return (lds_bytes - 4 * nwords) / 16; }
-
-int narrow_map_slots(int nwords, int lds_bytes) {
-    const int room = narrow_room(nwords, lds_bytes);
-    return room >= NARROW_MAP_MIN ? std::min(room, NARROW_MAP) : NARROW_MAP;
-}
+int64_t narrow_limit(int64_t slots) { return slots < NARROW_SLOTS ? NARROW_MAX : 0; }
 
 void launch_gr_narrow(const DevGraph& g, int lv0, int2* q0, int2* q1, DevCounters* ctr, const GrBits& bits,
                       long long max_slots, int lds_bytes, bool forward, hipStream_t st) {
-    const bool lbm = narrow_room(bits.nwords, lds_bytes) >= NARROW_MAP_MIN;
-    const int map = (int)std::min<long long>(narrow_map_slots(bits.nwords, lds_bytes), std::max(1ll, max_slots));
-    const size_t shm = 16 * (size_t)map + (lbm ? 4 * (size_t)bits.nwords : 0);
+    // the visited bitmap in LDS where it leaves room for two lists of pieces
+    const int64_t room = (lds_bytes - 4 * (int64_t)bits.nwords) / 16;
+    const bool lbm = room >= NARROW_CAP_MIN;
+    const int pieces = (int)std::min<int64_t>(lbm ? room : NARROW_CAP, NARROW_CAP);
+    const size_t shm = 16 * (size_t)pieces + (lbm ? 4 * (size_t)bits.nwords : 0);
     auto fn = forward ? (lbm ? k_gr_narrow<true, true> : k_gr_narrow<true, false>)
                       : (lbm ? k_gr_narrow<false, true> : k_gr_narrow<false, false>);
-    fn<<<1, NARROW_BLOCK, shm, st>>>(g, lv0, q0, q1, ctr, bits, max_slots, map);
+    fn<<<1, NARROW_BLOCK, shm, st>>>(g, lv0, q0, q1, ctr, bits, max_slots, pieces);
 }
 
 void launch_frontier_bitmap(const int2* q, int cnt, const GrBits& bits, int level, hipStream_t st) {

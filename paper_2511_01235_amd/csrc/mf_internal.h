@@ -134,7 +134,11 @@ constexpr int GR_STAGE_MIN = 1024;
 constexpr int BU_THREAD_SLOTS = 32;
 
 // Bitmaps of one global relabel: visited (nwords words), then a ring of
-// three frontier bitmaps (fb + r * nwords), all zeroed before each relabel.
+// three frontier bitmaps (fb + r * nwords), all zeroed before each relabel,
+// and on a graph handle the vertices with excess that a capped relabel counts
+// (fb + 3 * nwords, written by its init; a bit costs a cached word where the
+// excess itself is a memory trip per labelled vertex).
+constexpr int GR_BITMAPS = 5;
 struct GrBits {
     unsigned* visited;
     unsigned* fb;
@@ -324,8 +328,8 @@ void launch_gr_narrow(const DevGraph& g, int lv0, int2* q0, int2* q1, DevCounter
                       long long max_slots, int lds_bytes, bool forward, hipStream_t st);
 // dynamic LDS those launches may use on `device` (0: too little, never launch them)
 int narrow_lds_bytes(int device);
-// the largest frontier they take for bitmaps of nwords words
-int narrow_map_slots(int nwords, int lds_bytes);
+// the largest frontier they take in a graph of this many slots (0: never launch them)
+int64_t narrow_limit(int64_t slots);
 // BFS levels from lv0 in one cooperative launch of `grid` 1024-thread blocks
 // while the frontier covers at most max_slots slots (ctr->levels: where to
 // continue; ctr->bar_err set if a grid barrier gave up)
