@@ -1883,8 +1883,7 @@ mf_status mf_min_cut(mf_graph* g, uint8_t* source_side, int64_t* cut_capacity) {
         if (rc != MF_OK) return rc;
         g->heights_exact = true;
     }
-    mf::launch_fill_i32(reinterpret_cast<int32_t*>(g->cut_acc), 0, 2, st);
-    mf::launch_cut(g->dg, g->side, g->cut_acc, st);
+    mf::launch_cut(g->dg, g->side, g->cut_acc, g->wl[0], st);
     MF_HIP(hipGetLastError());
     unsigned long long c = 0;
     MF_HIP(hipMemcpyAsync(&c, g->cut_acc, sizeof(c), hipMemcpyDeviceToHost, st));

@@ -2973,16 +2973,22 @@ __global__ void __launch_bounds__(BS) k_batch_cleanup_multi(GraphUpdates* gu) {
 
 // ---- cut certificate --------------------------------------------------------
 
-// Latency-bound by its longest rows, so the slots are shared out, not the
-// vertices: a workgroup prefix-sums the row lengths of its 256 vertices and
-// consecutive threads take consecutive slots, four in flight each, the
-// neighbour's height gathered only where there is capacity.  (A thread per
-// row took 6.1 ms on RMAT-18, where one row holds 26,000 slots; this takes
-// 1.2 ms.)
+// Bound by its longest rows, so the slots are shared out, not the vertices: a
+// workgroup prefix-sums the row lengths of its 256 vertices and consecutive
+// threads take consecutive slots, four in flight each, the neighbour's height
+// gathered only where there is capacity.  Rows above CUT_LONG slots go to a
+// list that a second launch takes one workgroup per row: power-law graphs
+// have them side by side, and all of a workgroup's together would decide the
+// time.  (RMAT-18, one row of 26,000 slots: a thread per row 6.1 ms, shared
+// out without the list 1.2 ms, both launches
+// 0.13.)
 constexpr int CUT_U = 4;
+constexpr int CUT_LONG = 256;
+constexpr int CUT_BLOCK = 256;
 
-__global__ void __launch_bounds__(256) k_cut(DevGraph g, uint8_t* side, unsigned long long* cut) {
-    constexpr int BS = 256;
+__global__ void __launch_bounds__(CUT_BLOCK) k_cut(DevGraph g, uint8_t* side, unsigned long long* cut,
+                                                   int32_t* long_rows, int32_t* long_count) {
+    constexpr int BS = CUT_BLOCK;
     __shared__ int s_beg[BS], s_pre[BS + 1], s_w[BS / WAVE];
     const int N = g.n;
     const int tid = threadIdx.x;
@@ -2998,6 +3004,8 @@ __global__ void __launch_bounds__(256) k_cut(DevGraph g, uint8_t* side, unsigned
                 s_beg[tid] = g.row_ptr[v];
             }
         }
+        wave_append(len > CUT_LONG, v, long_rows, long_count);
+        if (len > CUT_LONG) len = 0;
         int wtot;
         const int wex = wave_excl_scan(len, &wtot);
         if (lane_id() == 0) s_w[tid / WAVE] = wtot;
@@ -3009,34 +3017,55 @@ __global__ void __launch_bounds__(256) k_cut(DevGraph g, uint8_t* side, unsigned
         }
         s_pre[tid] = woff + wex;
         __syncthreads();
-        for (int i0 = tid; i0 < total; i0 += CUT_U * BS) {
+        for (int i0 = 0; i0 < total; i0 += CUT_U * BS) {
             int32_t cp[CUT_U];
             int col[CUT_U];
 #pragma unroll
             for (int q = 0; q < CUT_U; ++q) {
-                const int i = i0 + q * BS;
-                cp[q] = 0;
-                col[q] = 0;
-                if (i < total) {
-                    int lo = 0, hi = BS;   // last staged row that starts at or before slot i
-                    while (hi - lo > 1) {
-                        const int mid = (lo + hi) >> 1;
-                        if (s_pre[mid] <= i) lo = mid;
-                        else hi = mid;
-                    }
-                    const int j = s_beg[lo] + (i - s_pre[lo]);
-                    cp[q] = g.cap[j];
-                    col[q] = g.cr[j].x;
+                const int i = min(i0 + q * BS + tid, total - 1);
+                int lo = 0, hi = BS;   // last staged row that starts at or before slot i
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (s_pre[mid] <= i) lo = mid;
+                    else hi = mid;
                 }
+                const int j = s_beg[lo] + (i - s_pre[lo]);
+                cp[q] = g.cap[j];
+                col[q] = g.cr[j].x;
             }
 #pragma unroll
             for (int q = 0; q < CUT_U; ++q)
-                if (cp[q] > 0 && g.h[col[q]] < N) c += cp[q];
+                if (i0 + q * BS + tid < total && cp[q] > 0 && g.h[col[q]] < N) c += cp[q];
         }
         __syncthreads();  // restaged next round
     }
     long long tot = block_sum_i64<BS>(c);
     if (tid == 0 && tot) atomicAdd(cut, (unsigned long long)tot);
+}
+
+__global__ void __launch_bounds__(CUT_BLOCK) k_cut_long(DevGraph g, unsigned long long* cut, const int32_t* long_rows,
+                                                        const int32_t* long_count) {
+    constexpr int BS = CUT_BLOCK;
+    const int N = g.n, rows = *long_count;
+    long long c = 0;
+    for (int r = blockIdx.x; r < rows; r += gridDim.x) {
+        const int v = long_rows[r], beg = g.row_ptr[v], end = beg + g.row_len[v];
+        for (int j0 = beg + (int)threadIdx.x; j0 < end; j0 += CUT_U * BS) {
+            int32_t cp[CUT_U];
+            int col[CUT_U];
+#pragma unroll
+            for (int q = 0; q < CUT_U; ++q) {
+                const int j = min(j0 + q * BS, end - 1);
+                cp[q] = g.cap[j];
+                col[q] = g.cr[j].x;
+            }
+#pragma unroll
+            for (int q = 0; q < CUT_U; ++q)
+                if (j0 + q * BS < end && cp[q] > 0 && g.h[col[q]] < N) c += cp[q];
+        }
+    }
+    long long tot = block_sum_i64<BS>(c);
+    if (threadIdx.x == 0 && tot) atomicAdd(cut, (unsigned long long)tot);
 }
 
 // ---- invariants of the residual state (diagnostics) ----------------------------
@@ -3875,8 +3904,11 @@ void launch_check_invariants(const DevGraph& g, unsigned long long* out, hipStre
     k_check_invariants<<<grid_for(g.n, 256, 4096), 256, 0, st>>>(g, out);
 }
 
-void launch_cut(const DevGraph& g, uint8_t* side, unsigned long long* cut, hipStream_t st) {
-    k_cut<<<grid_for(g.n, 256, 4096), 256, 0, st>>>(g, side, cut);
+void launch_cut(const DevGraph& g, uint8_t* side, unsigned long long* cut, int32_t* rows, hipStream_t st) {
+    int32_t* count = reinterpret_cast<int32_t*>(cut + 1);
+    launch_fill_i32(reinterpret_cast<int32_t*>(cut), 0, 4, st);
+    k_cut<<<grid_for(g.n, CUT_BLOCK, 4096), CUT_BLOCK, 0, st>>>(g, side, cut, rows, count);
+    k_cut_long<<<grid_for(g.n, 1, 2048), CUT_BLOCK, 0, st>>>(g, cut, rows, count);
 }
 
 void launch_batch_solve(GraphSlot* slots, const int32_t* order, int num, int mode, const GrTune& tune,

@@ -303,7 +303,8 @@ void launch_batch_clamp(const DevGraph& g, const mf_update* upd, int64_t k,
 // ctr not null: skipped when a row ran out of room (its demand stays in need[])
 void launch_batch_cleanup(BatchTable tb, int32_t* need, const int32_t* slot_of, int32_t* win,
                           int64_t k, const DevCounters* ctr, hipStream_t st);
-void launch_cut(const DevGraph& g, uint8_t* side, unsigned long long* cut, hipStream_t st);
+// side[v] = 1 where h[v] == n; cut[0] the capacity from there to the rest (cut[1] and rows[n]: scratch)
+void launch_cut(const DevGraph& g, uint8_t* side, unsigned long long* cut, int32_t* rows, hipStream_t st);
 // out[8] (device): negative residuals, broken pair sums, broken pair links,
 // excess mismatches, sum of excesses, heights out of range, steep residual
 // slots, active vertices
