@@ -357,25 +357,29 @@ mf_status ensure_snapshots(mf_graph* g) {
     return MF_OK;
 }
 
-// Allocate and upload the slot arrays of a Bi-CSR (plus the arrays whose size
-// follows the slot count).  res_init: residuals to upload, or empty for
-// res = cap (zero flow).
-mf_status upload_structure(mf_graph* g, const mf::HostBiCSR& b, const std::vector<int32_t>& res_init) {
+// The arrays whose size follows the slot count, besides the slots themselves.
+mf_status slot_scratch(mf_graph* g, int64_t S) {
+    g->q_cap = (int64_t)g->n + S / mf::GR_CHUNK + 64;
+    if (dalloc(g, &g->win, S) != hipSuccess || dalloc(g, &g->q[0], g->q_cap) != hipSuccess ||
+        dalloc(g, &g->q[1], g->q_cap) != hipSuccess)
+        return MF_ERR_OUT_OF_MEMORY;
+    mf::launch_fill_i32(g->win, -1, S, g->stream);
+    MF_HIP(hipGetLastError());
+    g->slot_cap = S;
+    return MF_OK;
+}
+
+// Allocate and upload a Bi-CSR built on the host (res = cap: zero flow).
+mf_status upload_structure(mf_graph* g, const mf::HostBiCSR& b) {
     const int32_t n = g->n;
     const int64_t S = b.row_ptr[(size_t)n];
-    if (dalloc(g, &g->dg.row_ptr, n + 1) != hipSuccess || dalloc(g, &g->dg.row_len, n) != hipSuccess ||
-        dalloc(g, &g->dg.row_sorted, n) != hipSuccess || dalloc(g, &g->dg.cr, S) != hipSuccess ||
-        dalloc(g, &g->dg.rev, S) != hipSuccess || dalloc(g, &g->dg.cap, S) != hipSuccess ||
-        dalloc(g, &g->dg.capsum, S) != hipSuccess ||
-        dalloc(g, &g->win, S) != hipSuccess)
-        return MF_ERR_OUT_OF_MEMORY;
-    g->q_cap = (int64_t)n + S / mf::GR_CHUNK + 64;
-    if (dalloc(g, &g->q[0], g->q_cap) != hipSuccess || dalloc(g, &g->q[1], g->q_cap) != hipSuccess)
+    if (dalloc(g, &g->dg.cr, S) != hipSuccess || dalloc(g, &g->dg.rev, S) != hipSuccess ||
+        dalloc(g, &g->dg.cap, S) != hipSuccess || dalloc(g, &g->dg.capsum, S) != hipSuccess)
         return MF_ERR_OUT_OF_MEMORY;
     std::vector<int2> cr((size_t)S);
     std::vector<int32_t> capsum((size_t)S, 0);
     for (int64_t j = 0; j < S; ++j) {
-        cr[(size_t)j] = make_int2(b.col[(size_t)j], res_init.empty() ? b.cap[(size_t)j] : res_init[(size_t)j]);
+        cr[(size_t)j] = make_int2(b.col[(size_t)j], b.cap[(size_t)j]);
         if (b.rev[(size_t)j] >= 0) capsum[(size_t)j] = b.cap[(size_t)j] + b.cap[(size_t)b.rev[(size_t)j]];
     }
     hipStream_t st = g->stream;
@@ -386,11 +390,42 @@ mf_status upload_structure(mf_graph* g, const mf::HostBiCSR& b, const std::vecto
     MF_HIP(hipMemcpyAsync(g->dg.rev, b.rev.data(), sizeof(int32_t) * S, hipMemcpyHostToDevice, st));
     MF_HIP(hipMemcpyAsync(g->dg.cap, b.cap.data(), sizeof(int32_t) * S, hipMemcpyHostToDevice, st));
     MF_HIP(hipMemcpyAsync(g->dg.capsum, capsum.data(), sizeof(int32_t) * S, hipMemcpyHostToDevice, st));
-    mf::launch_fill_i32(g->win, -1, S, st);
-    MF_HIP(hipGetLastError());
     MF_HIP(hipStreamSynchronize(st));  // host vectors die on return
-    g->slot_cap = S;
-    return MF_OK;
+    g->pairs = b.pairs;
+    g->m_unique = b.m_unique;
+    return slot_scratch(g, S);
+}
+
+// The graph's Bi-CSR in device memory: built there, or on the host where that
+// is faster or where the device lacks the memory to build it.  host: already
+// built there.
+mf_status load_structure(mf_graph* g, mf::HostBiCSR* host, int64_t m, const int32_t* src, const int32_t* dst,
+                         const int32_t* cap) {
+    const int32_t n = g->n;
+    if (dalloc(g, &g->dg.row_ptr, n + 1) != hipSuccess || dalloc(g, &g->dg.row_len, n) != hipSuccess ||
+        dalloc(g, &g->dg.row_sorted, n) != hipSuccess)
+        return MF_ERR_OUT_OF_MEMORY;
+    if (host) return upload_structure(g, *host);
+    mf::DeviceBiCSR b;
+    b.row_ptr = g->dg.row_ptr;
+    b.row_len = g->dg.row_len;
+    b.row_sorted = g->dg.row_sorted;
+    bool no_scratch = false;
+    mf_status rc = mf::build_bicsr_device(n, m, src, dst, cap, g->slack_min, g->slack_pct, g->stream, g->mem, &b,
+                                          &no_scratch);
+    g->dg.cr = b.a.cr;  // (released with the handle on an error)
+    g->dg.rev = b.a.rev;
+    g->dg.cap = b.a.cap;
+    g->dg.capsum = b.a.capsum;
+    if (no_scratch) {
+        mf::HostBiCSR hb;
+        rc = mf::build_bicsr(n, m, src, dst, cap, g->s, g->t, g->slack_min, g->slack_pct, &hb);
+        return rc != MF_OK ? rc : upload_structure(g, hb);
+    }
+    if (rc != MF_OK) return rc;
+    g->pairs = b.pairs;
+    g->m_unique = b.m_unique;
+    return slot_scratch(g, b.slots);
 }
 
 void free_host_copy(mf_graph* g) {
@@ -1644,9 +1679,14 @@ mf_status mf_graph_load(int32_t n, int64_t m, const int32_t* src, const int32_t*
     mf::Tuning tuning;
     if (mf::resolve_tuning(o, &tuning) != MF_OK) return MF_ERR_INVALID;
     if ((o.alloc == nullptr) != (o.free == nullptr)) return MF_ERR_INVALID;
+    if (!mf::bicsr_arguments_ok(n, m, src, dst, cap, s, t)) return MF_ERR_INVALID;
+    const bool on_device = m >= mf::BUILD_DEVICE_MIN && m < mf::BUILD_DEVICE_MAX;
     mf::HostBiCSR b;
-    mf_status rc = mf::build_bicsr(n, m, src, dst, cap, s, t, slack_min, slack_pct, &b);
-    if (rc != MF_OK) return rc;
+    mf_status rc = MF_OK;
+    if (!on_device) {
+        rc = mf::build_bicsr(n, m, src, dst, cap, s, t, slack_min, slack_pct, &b);
+        if (rc != MF_OK) return rc;
+    }
 
     mf_graph* g = new (std::nothrow) mf_graph();
     if (!g) return MF_ERR_OUT_OF_MEMORY;
@@ -1659,9 +1699,6 @@ mf_status mf_graph_load(int32_t n, int64_t m, const int32_t* src, const int32_t*
     g->t = t;
     g->slack_min = slack_min;
     g->slack_pct = slack_pct;
-    g->pairs = b.pairs;
-    g->m_unique = b.m_unique;
-    apply_tuning(g, tuning);
     g->push_pull = o.push_pull != 0;
     g->max_iter = o.max_iterations > 0 ? o.max_iterations : 4 * (int64_t)n + 1000;
     auto fail = [&](mf_status r) {
@@ -1670,16 +1707,25 @@ mf_status mf_graph_load(int32_t n, int64_t m, const int32_t* src, const int32_t*
         delete g;
         return r;
     };
+    // no usable device: edges are validated all the same
+    auto no_device = [&]() {
+        mf_status r = on_device ? mf::build_bicsr(n, m, src, dst, cap, s, t, slack_min, slack_pct, &b) : MF_OK;
+        return fail(r != MF_OK ? r : MF_ERR_DEVICE);
+    };
     int dev = o.device;
-    if (dev < 0 && hipGetDevice(&dev) != hipSuccess) return fail(MF_ERR_DEVICE);
-    if (hipSetDevice(dev) != hipSuccess) return fail(MF_ERR_DEVICE);
+    if (dev < 0 && hipGetDevice(&dev) != hipSuccess) return no_device();
+    if (hipSetDevice(dev) != hipSuccess) return no_device();
     g->device = dev;
     if (o.stream) {
         g->stream = (hipStream_t)o.stream;
     } else {
-        if (hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking) != hipSuccess) return fail(MF_ERR_DEVICE);
+        if (hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking) != hipSuccess) return no_device();
         g->own_stream = true;
     }
+    rc = load_structure(g, on_device ? nullptr : &b, m, src, dst, cap);
+    if (rc != MF_OK) return fail(rc);
+    b = mf::HostBiCSR();
+    apply_tuning(g, tuning);
     int cus = 256;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (dalloc(g, &g->dg.bytes_part, (int64_t)mf::KC_NCLASS * mf::BYTES_SLOTS) != hipSuccess)
@@ -1703,7 +1749,7 @@ mf_status mf_graph_load(int32_t n, int64_t m, const int32_t* src, const int32_t*
     g->dg.t = t;
     g->dg.root = t;
     g->dg.pinned = s;
-    g->dg.used_slots = b.pairs;
+    g->dg.used_slots = g->pairs;
     if (dalloc(g, &g->nslots_d, 2) != hipSuccess) return fail(MF_ERR_OUT_OF_MEMORY);
     g->dg.nslots = g->nslots_d;
     g->halt_d = reinterpret_cast<int32_t*>(g->nslots_d + 1);
@@ -1718,8 +1764,6 @@ mf_status mf_graph_load(int32_t n, int64_t m, const int32_t* src, const int32_t*
         return fail(MF_ERR_OUT_OF_MEMORY);
     if (hipHostMalloc((void**)&g->ctr_h, sizeof(DevCounters), hipHostMallocDefault) != hipSuccess)
         return fail(MF_ERR_OUT_OF_MEMORY);
-    rc = upload_structure(g, b, {});
-    if (rc != MF_OK) return fail(rc);
     rc = ensure_med(g, g->med);  // (needs q_cap)
     if (rc != MF_OK) return fail(rc);
     mf::launch_fill_i32(g->need, 0, n, g->stream);

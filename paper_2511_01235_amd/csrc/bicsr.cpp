@@ -66,11 +66,15 @@ void link_reverse(int32_t n, const std::vector<int32_t>& row_ptr, const std::vec
 
 }  // namespace
 
+bool bicsr_arguments_ok(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, const int32_t* cap, int32_t s,
+                        int32_t t) {
+    return n >= 2 && m >= 0 && s >= 0 && s < n && t >= 0 && t < n && s != t && (m == 0 || (src && dst && cap));
+}
+
 mf_status build_bicsr(int32_t n, int64_t m, const int32_t* src, const int32_t* dst,
                       const int32_t* cap, int32_t s, int32_t t, int32_t slack_min,
                       int32_t slack_pct, HostBiCSR* out) {
-    if (n < 2 || m < 0 || s < 0 || s >= n || t < 0 || t >= n || s == t) return MF_ERR_INVALID;
-    if (m > 0 && (!src || !dst || !cap)) return MF_ERR_INVALID;
+    if (!bicsr_arguments_ok(n, m, src, dst, cap, s, t)) return MF_ERR_INVALID;
     for (int64_t i = 0; i < m; ++i) {
         int32_t u = src[i], v = dst[i];
         if (u < 0 || u >= n || v < 0 || v >= n || u == v || cap[i] < 0) return MF_ERR_INVALID;

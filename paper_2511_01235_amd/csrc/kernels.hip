@@ -4001,13 +4001,22 @@ void launch_set_i64(long long* p, long long value, hipStream_t st) {
 
 int64_t relayout_tiles(int32_t V) { return ((int64_t)V + RL_TILE - 1) / RL_TILE; }
 
-void launch_relayout_plan(const RelayoutPlan& p, hipStream_t st) {
-    const int tiles = (int)relayout_tiles(p.V);
-    k_fill_i32<<<1, 64, 0, st>>>(p.sort_count, 0, 1);
-    k_relayout_sizes<<<(p.V + RL_BLOCK - 1) / RL_BLOCK, RL_BLOCK, 0, st>>>(p);
+void launch_scan_sizes(int32_t V, int64_t* size, int64_t* start, int64_t* tile, hipStream_t st) {
+    RelayoutPlan p{};
+    p.V = V;
+    p.size = size;
+    p.start = start;
+    p.tile = tile;
+    const int tiles = (int)relayout_tiles(V);
     k_relayout_tile_sums<<<tiles, RL_BLOCK, 0, st>>>(p);
     k_relayout_scan_tiles<<<1, RL_BLOCK, 0, st>>>(p, tiles);
     k_relayout_scan<<<tiles, RL_BLOCK, 0, st>>>(p);
+}
+
+void launch_relayout_plan(const RelayoutPlan& p, hipStream_t st) {
+    k_fill_i32<<<1, 64, 0, st>>>(p.sort_count, 0, 1);
+    k_relayout_sizes<<<(p.V + RL_BLOCK - 1) / RL_BLOCK, RL_BLOCK, 0, st>>>(p);
+    launch_scan_sizes(p.V, p.size, p.start, p.tile, st);
 }
 
 void launch_relayout_move(const RelayoutPlan& p, int32_t sort_count, int64_t S_new, SlotArrays from, SlotArrays to,

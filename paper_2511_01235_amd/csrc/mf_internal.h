@@ -383,6 +383,8 @@ void launch_round_terms_clear(DevCounters* ctr, hipStream_t st);
 // into round_e_t and round_deficit, and the deficient vertices above height
 // 0 into round_raised (all zeroed by that build).  Otherwise nothing.
 void launch_value_if_empty(const DevGraph& g, DevCounters* ctr, int guard_level, hipStream_t st);
+// exclusive scan of size[0..V) into start[0..V] (tile: relayout_tiles(V) words)
+void launch_scan_sizes(int32_t V, int64_t* size, int64_t* start, int64_t* tile, hipStream_t st);
 // sizes, their scan into start[] and the rows to sort; then the caller reads
 // start[V] (the new slot count) and *sort_count
 void launch_relayout_plan(const RelayoutPlan& p, hipStream_t st);
@@ -423,6 +425,31 @@ struct HostBiCSR {
 mf_status build_bicsr(int32_t n, int64_t m, const int32_t* src, const int32_t* dst,
                       const int32_t* cap, int32_t s, int32_t t, int32_t slack_min,
                       int32_t slack_pct, HostBiCSR* out);
+
+// Whether build_bicsr takes these arguments at all (the edges are not read).
+bool bicsr_arguments_ok(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, const int32_t* cap, int32_t s,
+                        int32_t t);
+
+// ---- device Bi-CSR builder (build.hip) -----------------------------------
+// Edge counts it takes.  Below the minimum the host builder is no slower than
+// the thirty launches and two read-backs (whole loads of 2,000 / 4,000 /
+// 16,000 edges on the host: 0.31 / 0.40 / 1.08 ms; 16,000 on the device: 0.35);
+// above the maximum the entries would not fit 32-bit indices.
+constexpr int64_t BUILD_DEVICE_MIN = 4096;
+constexpr int64_t BUILD_DEVICE_MAX = 1ll << 30;
+struct DeviceBiCSR {
+    int32_t *row_ptr = nullptr, *row_len = nullptr, *row_sorted = nullptr;  // the caller's: n + 1, n and n words
+    SlotArrays a{nullptr, nullptr, nullptr, nullptr};                       // allocated here, the caller's to release
+    int64_t slots = 0, pairs = 0, m_unique = 0;
+};
+// The same graph as build_bicsr with res = cap, on the device; arguments
+// checked by bicsr_arguments_ok.  Same errors, MF_ERR_OUT_OF_MEMORY
+// (*no_scratch: for its scratch, about 76 bytes per edge taken with hipMalloc
+// for the call; the host builder needs none) and MF_ERR_DEVICE; the stream is
+// idle on return.
+mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, const int32_t* cap,
+                             int32_t slack_min, int32_t slack_pct, hipStream_t st, const DeviceAllocator& mem,
+                             DeviceBiCSR* out, bool* no_scratch);
 
 // Device relayout (relayout.cpp): runs the plan, allocates the new slot
 // arrays, moves the slots and frees the old arrays; *arrays and *S_new then
