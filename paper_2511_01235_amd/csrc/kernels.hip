@@ -617,6 +617,8 @@ __global__ void __launch_bounds__(256) k_gr_init(DevGraph g, int2* q0, DevCounte
 // Top-down slots per thread per round (loads in flight, and one queue atomic
 // per block per GR_TD_U * BS slots).
 constexpr int GR_TD_U = 4;
+// Bottom-up: slots in flight per lane in the rows a wave finishes.
+constexpr int BU_WAVE_U = 2;
 
 // A vertex gets height lv+1: mark it visited and in the next frontier, queue
 // its entries, and return its slot count for the direction counters.
@@ -659,6 +661,36 @@ __device__ __forceinline__ int discover(const DevGraph& g, DevCounters* ctr, con
     int len = g.row_len[v];
     *add = (len + GR_CHUNK - 1) / GR_CHUNK;
     return len;
+}
+
+// Bottom-up: whether one of the slots beg..end of a row leads (with the
+// residual the level needs) to a vertex of bitmap bm; U slots at a time, all
+// their loads issued before the first is used (a load under a branch would be
+// waited for inside it: a slot past the end reads the last one).
+template <bool FWD, int U>
+__device__ __forceinline__ bool row_hit(const DevGraph& g, const unsigned* bm, int beg, int end,
+                                        unsigned long long* scanned) {
+    bool hit = false;
+    for (int j = beg; j < end && !hit; j += U) {
+        int2 c[U];
+        int32_t r[U];
+        unsigned w[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int i = min(j + q, end - 1);
+            c[q] = g.cr[i];
+            r[q] = FWD ? g.capsum[i] : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) w[q] = bm[c[q].x >> 5];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int32_t x = FWD ? r[q] - c[q].y : c[q].y;  // (the last slot again: no other answer)
+            hit = hit || (x > 0 && (w[q] >> (c[q].x & 31) & 1u));
+        }
+        *scanned += (unsigned long long)min(U, end - j);
+    }
+    return hit;
 }
 
 // The work of one level for a block of BS threads; cnt = the frontier size.
@@ -787,34 +819,8 @@ __device__ __forceinline__ void gr_level_body(const Par& P, const DevGraph& g, i
                 int beg = g.row_ptr[v], len = g.row_len[v];
                 int end = beg + min(len, BU_THREAD_SLOTS);
                 exam += 2;  // the row bounds
-                bool hit = false;
-                if (bu_wide) {
-                    for (int j = beg; j < end && !hit; j += 8) {
-                        int2 c8[8];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) c8[q] = j + q < end ? g.cr[j + q] : make_int2(0, 0);
-                        int32_t r8[8];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q)
-                            r8[q] = j + q < end ? (FWD ? g.capsum[j + q] - c8[q].y : c8[q].y) : 0;
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) hit = hit || (r8[q] > 0 && at_level(c8[q].x));
-                        scanned += (unsigned long long)min(8, end - j);
-                    }
-                } else {
-                    for (int j = beg; j < end && !hit; j += 4) {
-                        int2 c4[4];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) c4[q] = j + q < end ? g.cr[j + q] : make_int2(0, 0);
-                        int32_t r4[4];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            r4[q] = j + q < end ? (FWD ? g.capsum[j + q] - c4[q].y : c4[q].y) : 0;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) hit = hit || (r4[q] > 0 && at_level(c4[q].x));
-                        scanned += (unsigned long long)min(4, end - j);
-                    }
-                }
+                const bool hit = bu_wide ? row_hit<FWD, 8>(g, bm_level, beg, end, &scanned)
+                                         : row_hit<FWD, 4>(g, bm_level, beg, end, &scanned);
                 if (hit) {
                     g.h[v] = lv + 1;
                     reached(g, bits, ctr, lv, v);
@@ -844,15 +850,24 @@ __device__ __forceinline__ void gr_level_body(const Par& P, const DevGraph& g, i
                 int w = s_defer[d];
                 int beg = g.row_ptr[w] + BU_THREAD_SLOTS, end = g.row_ptr[w] + g.row_len[w];
                 bool hit = false;
-                for (int b = beg; b < end; b += WAVE) {
-                    int j = b + lane;
+                for (int b = beg; b < end; b += BU_WAVE_U * WAVE) {
+                    int2 c[BU_WAVE_U];
+                    int32_t r[BU_WAVE_U];
+                    unsigned bw[BU_WAVE_U];
                     bool my = false;
-                    if (j < end) {
-                        int2 c = g.cr[j];
-                        int32_t r = FWD ? g.capsum[j] - c.y : c.y;
-                        my = r > 0 && at_level(c.x);
+#pragma unroll
+                    for (int q = 0; q < BU_WAVE_U; ++q) {
+                        const int j = min(b + q * WAVE + lane, end - 1);
+                        c[q] = g.cr[j];
+                        r[q] = FWD ? g.capsum[j] : 0;
                     }
-                    scanned += (unsigned long long)(j < end);
+#pragma unroll
+                    for (int q = 0; q < BU_WAVE_U; ++q) bw[q] = bm_level[c[q].x >> 5];
+#pragma unroll
+                    for (int q = 0; q < BU_WAVE_U; ++q) {
+                        my = my || ((FWD ? r[q] - c[q].y : c[q].y) > 0 && (bw[q] >> (c[q].x & 31) & 1u));
+                        scanned += (unsigned long long)(b + q * WAVE + lane < end);
+                    }
                     if (__ballot(my)) {
                         hit = true;
                         break;
@@ -901,29 +916,54 @@ __device__ __forceinline__ void gr_level_body(const Par& P, const DevGraph& g, i
             scanned += (unsigned long long)total;  // counted once per block (thread 0 below)
             for (int base = 0; base < total; base += GR_TD_U * BS) {
                 int vs[GR_TD_U], adds[GR_TD_U], lens[GR_TD_U];
-                int2 cr[GR_TD_U];
                 int32_t r[GR_TD_U];
+                // every load of the U slots before the first is used, then
+                // every visited word, every CAS, every row length (no load
+                // under a branch that also uses it, where it would be waited
+                // for: a slot past the end reads the last one)
+                {
+                    int2 cr[GR_TD_U];
+                    int32_t sum[GR_TD_U];
 #pragma unroll
-                for (int k = 0; k < GR_TD_U; ++k) {  // the loads of all U slots first
-                    const int i = base + k * BS + tid;
-                    cr[k] = make_int2(-1, 0);
-                    r[k] = 0;
-                    if (i < total) {
+                    for (int k = 0; k < GR_TD_U; ++k) {
+                        const int i = min(base + k * BS + tid, total - 1);
                         const int lo = owner(i);
                         const int j = s_beg[lo] + (i - s_pre[lo]);
                         cr[k] = g.cr[j];
-                        r[k] = FWD ? cr[k].y : g.capsum[j] - cr[k].y;
+                        sum[k] = FWD ? 0 : g.capsum[j];
+                    }
+#pragma unroll
+                    for (int k = 0; k < GR_TD_U; ++k) {
+                        vs[k] = cr[k].x;
+                        r[k] = base + k * BS + tid < total ? (FWD ? cr[k].y : sum[k] - cr[k].y) : 0;
+                    }
+                }
+                unsigned seen[GR_TD_U];
+                int old[GR_TD_U];
+#pragma unroll
+                for (int k = 0; k < GR_TD_U; ++k) seen[k] = bm_seen[vs[k] >> 5];  // pinned is marked visited at init
+#pragma unroll
+                for (int k = 0; k < GR_TD_U; ++k) {
+                    old[k] = 0;
+                    if (r[k] > 0 && !(seen[k] >> (vs[k] & 31) & 1u)) old[k] = atomicCAS(&g.h[vs[k]], N, lv + 1);
+                }
+                unsigned ex[GR_TD_U];
+#pragma unroll
+                for (int k = 0; k < GR_TD_U; ++k) {
+                    lens[k] = 0;
+                    ex[k] = 0u;
+                    if (old[k] == N) {
+                        lens[k] = g.row_len[vs[k]];
+                        if (g.bfs_cap) ex[k] = bits.fb[3 * (size_t)bits.nwords + (vs[k] >> 5)];
                     }
                 }
 #pragma unroll
                 for (int k = 0; k < GR_TD_U; ++k) {
-                    const int v = cr[k].x;
-                    vs[k] = v;
-                    adds[k] = 0;
-                    lens[k] = 0;
-                    // pinned is marked visited at init
-                    if (r[k] > 0 && !bit_of(bm_seen, v) && atomicCAS(&g.h[v], N, lv + 1) == N) {
-                        lens[k] = discover(g, ctr, bits, lv, v, &adds[k]);
+                    adds[k] = (lens[k] + GR_CHUNK - 1) / GR_CHUNK;
+                    if (old[k] == N) {
+                        set_bit(bits.visited, vs[k]);
+                        set_bit(bits.fb + (size_t)((lv + 1) % 3) * bits.nwords, vs[k]);
+                        if (ex[k] >> (vs[k] & 31) & 1u) atomicAdd(&ctr->bfs_disc[(lv + 1) % 3], 1);
                         found++;
                     }
                 }
@@ -1016,7 +1056,9 @@ __global__ void __launch_bounds__(BS) k_gr_level(DevGraph g, int lv, const int2*
                                                  DevCounters* ctr, GrBits bits, GrTune tune) {
     if (halted(g)) return;
     extern __shared__ unsigned s_dyn[];
-    gr_level_step<FWD, BS>(hw_par(), g, lv, qin, qout, ctr, bits, tune, tune.lds ? s_dyn : nullptr);
+    // (known at compile time where no bitmap is staged: global loads, not flat ones)
+    gr_level_step<FWD, BS>(hw_par(), g, lv, qin, qout, ctr, bits, tune,
+                           BS == GRL_BLOCK_LDS && tune.lds ? s_dyn : nullptr);
 }
 
 // Barrier of a workgroup whose waves share LDS only: it does not wait for
