@@ -840,10 +840,17 @@ __device__ __forceinline__ void gr_level_body(const Par& P, const DevGraph& g, i
                     atomicOr(&bits.fb[(size_t)((lv + 1) % 3) * bits.nwords + (v >> 5)], half);
                 }
             }
-            {   // block_append's barriers also publish s_defer / s_ndefer
+            {   // block_append's barriers also publish s_defer / s_ndefer;
+                // wave_append has none, and a wave that read the list before
+                // the last one wrote to it would miss rows or take an entry
+                // not yet written for a vertex
                 const int vs[1] = {v}, adds[1] = {add}, lens[1] = {slots};
-                if (AGG) block_append<BS, 1>(vs, adds, lens, qout, out_cnt, s_agg);
-                else wave_append<1>(vs, adds, lens, qout, out_cnt);
+                if (AGG) {
+                    block_append<BS, 1>(vs, adds, lens, qout, out_cnt, s_agg);
+                } else {
+                    wave_append<1>(vs, adds, lens, qout, out_cnt);
+                    __syncthreads();
+                }
             }
             const int nd = s_ndefer;
             for (int d = tid / WAVE; d < nd; d += BS / WAVE) {
