@@ -205,6 +205,13 @@ __device__ __forceinline__ unsigned long long group_min(unsigned long long x) {
         return x;
     }
 }
+// the group's first lane's copy
+template <int G>
+__device__ __forceinline__ int64_t group_first(int64_t x) {
+    static_assert(G == 4 || G == WAVE, "a quad permutation, or the wave's first lane");
+    if constexpr (G == WAVE) return bcast64(x);
+    else return (int64_t)dpp_move<0x00>((unsigned long long)x);
+}
 template <int G>
 __device__ __forceinline__ long long group_sum(long long x0) {
     unsigned long long x = (unsigned long long)x0;
@@ -2068,6 +2075,10 @@ __device__ __forceinline__ unsigned long long pr_group(const DevGraph& g, const 
         hu = g.h[u];
         eu = amount<PULL>(g, u);
     }
+    // one amount for the whole group: the lanes' loads may be served by
+    // different trips, with another row's push to u between them, and the
+    // pushes would then not add up to what leaves e(u)
+    eu = group_first<G>(eu);
     int col[SL], rj[SL];
     int32_t r[SL];
     {

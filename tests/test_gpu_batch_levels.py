@@ -46,3 +46,21 @@ def test_batched_bottom_up_deferred_rows(device, block):
         assert B.maxflow().tolist() == want
         batches = [st.next_batch(max(1, g.m // 50)) for g, st in zip(graphs, streams)]
         assert B.apply(batches).tolist() == [o.apply(*b) for o, b in zip(oracles, batches)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [257, 700, 1500])
+def test_rows_pushed_to_while_they_push(device, rows):
+    """B's vertices push to one another as well as to A: what the lanes of a
+    row push together is what leaves its vertex, whatever arrives meanwhile."""
+    g = deferred_rows_graph(rows, 61000 + rows)
+    o = oracle.DynOracle(g.n, g.src, g.dst, g.cap, g.s, g.t)
+    st = gen.BatchStream(g, 61200 + rows, inc_max=10, new_cap_max=20)
+    print(f"[test] rows pushed to meanwhile, {rows} rows", flush=True)
+    with mf.MaxFlowGraph(g.n, g.src, g.dst, g.cap, g.s, g.t) as G:
+        assert G.maxflow() == o.static()
+        for _ in range(3):
+            batch = st.next_batch(max(1, g.m // 20))
+            assert G.apply_batch(*batch) == o.apply(*batch)
+        inv = G.invariants()
+        assert not any(inv[k] for k in ("negative_residuals", "pair_sums", "pair_links", "excess_mismatches"))
