@@ -1186,7 +1186,8 @@ __device__ __forceinline__ void narrow_put(const int (&vs)[U], const int (&beg)[
         }
         const unsigned incl = wave_incl_add(mine), isl = wave_incl_add(sl);
         cnt = lane63(incl);
-        if (lane_id() == 0) base = (unsigned)atomicAdd(o.front, ((unsigned long long)lane63(isl) << 32) | cnt);
+        const unsigned long long slots = lane63(isl);
+        if (lane_id() == 0) base = (unsigned)atomicAdd(o.front, slots << 32 | cnt);
         base = (unsigned)bcast((int)base);
         if ((unsigned long long)base + cnt <= (unsigned)o.cap) {
             unsigned at = base + incl - mine;

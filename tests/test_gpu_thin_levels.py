@@ -1,0 +1,91 @@
+"""BFS levels and push-relabel rounds that one workgroup runs from LDS lists,
+and the cut's long rows, at the sizes where a list, a piece of a row or a
+bitmap word ends: layered graphs whose levels have a given width and rows a
+given length.  Heights against the oracle's, values and cuts exact."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2511_01235_amd as mf
+from paper_2511_01235_amd import gen
+
+
+def ring_layers(width, out, layers, seed):
+    """s -> layers of `width` vertices -> t, vertex a to a .. a + out - 1 (mod
+    width) of the next layer: rows of 2 * out slots between the layers."""
+    rng = gen.rng_for(seed)
+    a = np.arange(width)
+    n = 2 + width * layers
+    u, v = [np.zeros(width, np.int64)], [1 + a]
+    for i in range(layers - 1):
+        for d in range(min(out, width)):
+            u.append(1 + i * width + a)
+            v.append(1 + (i + 1) * width + (a + d) % width)
+    u.append(1 + (layers - 1) * width + a)
+    v.append(np.full(width, n - 1))
+    u, v = np.concatenate(u), np.concatenate(v)
+    c = rng.integers(1, 30, u.size)
+    return gen.Graph(f"ring_{width}_{out}", n, u.astype(np.int32), v.astype(np.int32), c.astype(np.int32), 0, n - 1)
+
+
+def fan(top, levels, seed):
+    """s -> top vertices, each to two of a layer twice as wide, and so on; the
+    last layer -> t: a round's list doubles from layer to layer."""
+    rng = gen.rng_for(seed)
+    u, v, c = [np.zeros(top, np.int64)], [1 + np.arange(top)], [np.full(top, 1 << (levels + 2))]
+    first, width = 1, top
+    for i in range(levels):
+        a = np.arange(width)
+        for d in (0, 1):
+            u.append(first + a)
+            v.append(first + width + 2 * a + d)
+            c.append(rng.integers(1, (1 << (levels + 1 - i)) + 1, width))
+        first, width = first + width, 2 * width
+    n = first + width + 1
+    u.append(first + np.arange(width))
+    v.append(np.full(width, n - 1))
+    c.append(rng.integers(1, 4, width))
+    u, v, c = np.concatenate(u), np.concatenate(v), np.concatenate(c)
+    return gen.Graph(f"fan_{top}_{levels}", n, u.astype(np.int32), v.astype(np.int32), c.astype(np.int32), 0, n - 1)
+
+
+# rows of 4, 32, 34 and 40 slots: one piece, eight, nine and ten; 2047 to 2049
+# and 4095 to 4097 pieces of a level; 8184 to 8200 slots; s and t rows of 255 to
+# 257 slots (the cut's long ones from 257 on); one vertex wide, and a wave wide
+GRAPHS = [("ring", 1, 1, 40), ("ring", 64, 2, 9), ("ring", 40, 16, 5), ("ring", 40, 17, 5), ("ring", 33, 20, 4),
+          ("ring", 255, 2, 4), ("ring", 256, 2, 4), ("ring", 257, 2, 4), ("ring", 1023, 4, 4), ("ring", 1024, 4, 4),
+          ("ring", 1025, 4, 4), ("ring", 2047, 2, 3), ("ring", 2049, 2, 3), ("ring", 4095, 1, 3), ("ring", 4096, 1, 3),
+          ("ring", 4097, 1, 3), ("fan", 500, 4), ("fan", 2048, 2)]
+
+
+def make(spec, seed):
+    return ring_layers(*spec[1:], seed) if spec[0] == "ring" else fan(*spec[1:], seed)
+
+
+@pytest.fixture(scope="module")
+def device():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible MI355X"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("spec", GRAPHS, ids=lambda s: "_".join(map(str, s)))
+def test_thin_levels_and_rounds(device, spec):
+    g = make(spec, 63000)
+    h_want, _ = oracle.DynOracle(g.n, g.src, g.dst, g.cap, g.s, g.t).initial_labels()
+    o = oracle.DynOracle(g.n, g.src, g.dst, g.cap, g.s, g.t)
+    want = o.static()
+    batch = gen.BatchStream(g, 63100, inc_max=20, new_cap_max=20).next_batch(max(1, g.m // 50))
+    after = o.apply(*batch)
+    print(f"[test] thin levels {g.name} n={g.n}", flush=True)
+    # one workgroup as far as it goes, and the defaults
+    for opt in (dict(bfs_narrow_slots=8192, round_narrow=4096), {}):
+        with mf.MaxFlowGraph(g.n, g.src, g.dst, g.cap, g.s, g.t, **opt) as G:
+            assert np.array_equal(G.initial_labels()[0], h_want)
+        with mf.MaxFlowGraph(g.n, g.src, g.dst, g.cap, g.s, g.t, **opt) as G:
+            assert G.maxflow() == want
+            side, cut = G.min_cut()
+            assert cut == want and side[g.s] == 1 and side[g.t] == 0
+            assert oracle.cert_check(g.n, g.src, g.dst, g.cap, g.s, g.t, None, side, want)[0] == 0
+            assert G.apply_batch(*batch) == after
+            assert G.min_cut()[1] == after
