@@ -9,8 +9,10 @@
 //                                  source pinned at |V|)
 //   k_build_worklist               active-vertex worklist (Section 5.2, O1)
 //                                  plus the value reduction of Algorithm 5
-//   k_pr_{thread,wave,block}       push-relabel kernel, Algorithm 2
-//   k_rie_{thread,wave,block}      remove-invalid-edges kernel, Algorithm 3
+//   k_pr_small, k_pr_block         push-relabel kernel, Algorithm 2
+//   k_rie_round                    remove-invalid-edges kernel, Algorithm 3
+//   k_gr_narrow, k_rounds_narrow   the same levels and rounds while one
+//                                  workgroup holds their lists in LDS
 //   k_batch_*                      update apply and clamp of Algorithm 5
 //   k_cut                          cut certificate of Sections 3.1 / 4.3
 //
@@ -3348,9 +3350,9 @@ __global__ void __launch_bounds__(256) k_value_if_empty(DevGraph g, DevCounters*
 // steep slots), 7.5 now.  Without LBM (more vertices than bits in LDS) the
 // repeats are found with mark[v] == epoch.
 //
-// Lists alternate between the two halves; input in a0, a1 with counts in
-// ctr->wl; on exit the list to run next is in set a, its counts in ctr->wl,
-// ctr->rn_set 0 and ctr->rn_rounds the rounds run.  Activations of the last
+// Lists alternate between two halves of LDS; input in a0, a1 with counts in
+// ctr->wl; on exit the list to run next is there too, its counts in
+// ctr->wl and the rounds run in ctr->rn_rounds.  Activations of the last
 // round are already in that list (the caller clears the activation count).
 constexpr int RN_BLOCK = 1024;
 constexpr int RN_MAX = 4096;     // vertices of a list
@@ -3377,7 +3379,6 @@ __global__ void __launch_bounds__(RN_BLOCK) k_rounds_narrow(DevGraph g, int32_t*
     int ep = *epoch;
     if (c2 != 0 || c0 + c1 == 0 || c0 + c1 > limit || max_rounds <= 0) {
         if (tid == 0) {
-            ctr->rn_set = 0;
             ctr->rn_rounds = 0;
         }
         return;
@@ -3505,7 +3506,6 @@ __global__ void __launch_bounds__(RN_BLOCK) k_rounds_narrow(DevGraph g, int32_t*
         ctr->wl[1] = c1;
         ctr->wl[2] = c2;
         ctr->wl[3] = c0 + c1 + c2;
-        ctr->rn_set = 0;
         ctr->rn_rounds = r;
         *epoch = ep;
     }

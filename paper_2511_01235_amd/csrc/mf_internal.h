@@ -85,8 +85,7 @@ struct DevCounters {
     long long round_deficit;   // e(t) and the sum of negative excess outside {s,t}
     int32_t round_raised;      // ... and the deficient vertices above height 0 (made by remove-invalid-
                                //     edges after the relabel); the loop may end there only if none
-    int32_t rn_set;            // one-workgroup rounds: which list set holds the next list (0 in, 1 other)
-    int32_t rn_rounds;         // ... and how many rounds they ran
+    int32_t rn_rounds;         // one-workgroup rounds: how many the last launch ran
     int32_t bfs_total;         // capped relabel: vertices with excess (counted by the init)
     int32_t bfs_disc[3];       // ... of them labelled at level lv, in bfs_disc[lv % 3]
     int32_t bfs_cum[3];        // ... labelled at levels <= lv, in bfs_cum[lv % 3]
@@ -103,8 +102,8 @@ struct DevCounters {
 // one-workgroup thin-frontier levels
 enum KernelClass { KC_GR = 0, KC_PR = 1, KC_RIE = 2, KC_WL = 3, KC_BATCH = 4, KC_INIT = 5, KC_GRS = 6, KC_NCLASS = 8 };
 
-// Default degree bins for the worklist: rows up to BIN0_MAX slots get one
-// thread, up to BIN1_MAX one wave, longer rows one 1024-thread block.
+// Default degree bins for the worklist: rows up to BIN0_MAX slots get a
+// group of lanes, up to BIN1_MAX one wave, longer rows one 1024-thread block.
 constexpr int BIN0_MAX = 16;
 constexpr int BIN1_MAX = 512;
 constexpr int BLOCK_PR = 1024;
