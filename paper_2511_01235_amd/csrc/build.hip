@@ -19,6 +19,7 @@
 #include <cstdint>
 
 #include "mf_internal.h"
+#include "slot_index.h"
 
 namespace mf {
 
@@ -252,14 +253,15 @@ __global__ void __launch_bounds__(BLOCK) k_build_row_ptr(int n, const int64_t* s
 // free slots: {own row, 0}, unlinked (eight lanes per row)
 __global__ void __launch_bounds__(BLOCK) k_build_slack(int n, const int32_t* row_ptr, const int32_t* row_len,
                                                        SlotArrays a) {
-    const int64_t t = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    const int v = (int)(t / 8);
-    if (v >= n) return;
-    for (int j = row_ptr[v] + row_len[v] + (int)(t % 8); j < row_ptr[v + 1]; j += 8) {
-        a.cr[j] = make_int2(v, 0);
-        a.rev[j] = -1;
-        a.cap[j] = 0;
-        a.capsum[j] = 0;
+    const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    for (int64_t t = (int64_t)blockIdx.x * BLOCK + threadIdx.x; t < 8 * (int64_t)n; t += stride) {
+        const int v = (int)(t / 8);
+        strided((int64_t)row_ptr[v] + row_len[v] + t % 8, row_ptr[v + 1], 8, [&](int j) {
+            a.cr[j] = make_int2(v, 0);
+            a.rev[j] = -1;
+            a.cap[j] = 0;
+            a.capsum[j] = 0;
+        });
     }
 }
 
@@ -276,12 +278,7 @@ __global__ void __launch_bounds__(BLOCK) k_build_slots(int64_t entries, int bits
         const unsigned long long k = mkey[e];
         const int u = (int)(k >> bits), v = (int)(k & low);
         const unsigned long long back = (unsigned long long)(unsigned)v << bits | (unsigned)u;
-        int lo = first[v], hi = end[v];
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (mkey[mid] < back) lo = mid + 1;
-            else hi = mid;
-        }
+        const int lo = first_at_least(mkey, first[v], end[v], back);
         const int j = row_ptr[u] + (int)(e - first[u]), jr = row_ptr[v] + (lo - first[v]);
         const unsigned long long c = sum[e], both = c + sum[lo];
         if (both > (unsigned long long)INT_MAX) bc->overflow = 1;
@@ -403,7 +400,7 @@ mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int
         mem.allocate((void**)&out->a.capsum, 4 * (size_t)S) != hipSuccess)
         return MF_ERR_OUT_OF_MEMORY;
     k_build_row_ptr<<<blocks_for((int64_t)n + 1, BLOCK), BLOCK, 0, st>>>(n, start, out->row_ptr);
-    k_build_slack<<<blocks_for(8 * (int64_t)n, BLOCK), BLOCK, 0, st>>>(n, out->row_ptr, out->row_len, out->a);
+    k_build_slack<<<stride_blocks(8 * (int64_t)n, BLOCK), BLOCK, 0, st>>>(n, out->row_ptr, out->row_len, out->a);
     k_build_slots<<<blocks_for(c.entries, BLOCK), BLOCK, 0, st>>>(c.entries, bits, mkey, sum, first, end,
                                                                   out->row_ptr, out->a, bc);
     BUILD_HIP(hipGetLastError());
