@@ -32,6 +32,7 @@
 
 #include "mf.h"
 #include "mf_internal.h"
+#include "slot_index.h"
 
 namespace mf {
 
@@ -3113,19 +3114,19 @@ __global__ void __launch_bounds__(CUT_BLOCK) k_cut_long(DevGraph g, unsigned lon
     long long c = 0;
     for (int r = blockIdx.x; r < rows; r += gridDim.x) {
         const int v = long_rows[r], beg = g.row_ptr[v], end = beg + g.row_len[v];
-        for (int j0 = beg + (int)threadIdx.x; j0 < end; j0 += CUT_U * BS) {
+        strided((int64_t)beg + threadIdx.x, end, CUT_U * BS, [&](int64_t j0) {
             int32_t cp[CUT_U];
             int col[CUT_U];
 #pragma unroll
             for (int q = 0; q < CUT_U; ++q) {
-                const int j = min(j0 + q * BS, end - 1);
+                const int j = slot_or_last(j0 + q * BS, end);
                 cp[q] = g.cap[j];
                 col[q] = g.cr[j].x;
             }
 #pragma unroll
             for (int q = 0; q < CUT_U; ++q)
                 if (j0 + q * BS < end && cp[q] > 0 && g.h[col[q]] < N) c += cp[q];
-        }
+        });
     }
     long long tot = block_sum_i64<BS>(c);
     if (threadIdx.x == 0 && tot) atomicAdd(cut, (unsigned long long)tot);

@@ -24,6 +24,9 @@ constexpr void strided(int64_t beg, int64_t end, int step, F f) {
     for (int64_t j = beg; j < end; j += step) f((int)j);
 }
 
+// Slot j of a row that ends at `end`, or the row's last one.
+constexpr int slot_or_last(int64_t j, int end) { return j < end ? (int)j : end - 1; }
+
 // Workgroups of `block` threads for `items` threads of work in a grid-stride
 // loop.  A launch takes fewer than 2^32 threads in all.
 constexpr unsigned stride_blocks(int64_t items, int block) {

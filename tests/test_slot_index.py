@@ -57,6 +57,17 @@ int main() {
             }
 }
 """,
+    # a workgroup's loads past the end of such a row read its last slot
+    "last": r"""
+int main() {
+    for (int end : {INT_MAX, INT_MAX - 1, 5})
+        for (int j0 : {end - 4, end - 1})
+            for (int off : {0, 1, 3, 256, 768, 1024}) {
+                const int j = mf::slot_or_last((int64_t)j0 + off, end);
+                CHECK(j >= j0 && j < end && (j == end - 1 || j == j0 + off));
+            }
+}
+""",
     # 8 threads for each of up to INT_MAX vertices
     "blocks": r"""
 int main() {
