@@ -397,8 +397,8 @@ mf_status upload_structure(mf_graph* g, const mf::HostBiCSR& b) {
 }
 
 // The graph's Bi-CSR in device memory: built there, or on the host where that
-// is faster or where the device lacks the memory to build it.  host: already
-// built there.
+// is faster or where the device lacks the memory to build it beside the
+// handle.  host: already built there.
 mf_status load_structure(mf_graph* g, mf::HostBiCSR* host, int64_t m, const int32_t* src, const int32_t* dst,
                          const int32_t* cap) {
     const int32_t n = g->n;
@@ -410,14 +410,18 @@ mf_status load_structure(mf_graph* g, mf::HostBiCSR* host, int64_t m, const int3
     b.row_ptr = g->dg.row_ptr;
     b.row_len = g->dg.row_len;
     b.row_sorted = g->dg.row_sorted;
-    bool no_scratch = false;
+    bool no_room = false;
     mf_status rc = mf::build_bicsr_device(n, m, src, dst, cap, g->slack_min, g->slack_pct, g->stream, g->mem, &b,
-                                          &no_scratch);
+                                          &no_room);
     g->dg.cr = b.a.cr;  // (released with the handle on an error)
     g->dg.rev = b.a.rev;
     g->dg.cap = b.a.cap;
     g->dg.capsum = b.a.capsum;
-    if (no_scratch) {
+    if (no_room) {
+        dfree(g, g->dg.cr);
+        dfree(g, g->dg.rev);
+        dfree(g, g->dg.cap);
+        dfree(g, g->dg.capsum);
         mf::HostBiCSR hb;
         rc = mf::build_bicsr(n, m, src, dst, cap, g->s, g->t, g->slack_min, g->slack_pct, &hb);
         return rc != MF_OK ? rc : upload_structure(g, hb);

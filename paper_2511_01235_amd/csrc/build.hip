@@ -293,6 +293,11 @@ __global__ void __launch_bounds__(BLOCK) k_build_slots(int64_t entries, int bits
     if (threadIdx.x == 0 && total) atomicAdd(&bc->with_capacity, (unsigned long long)total);
 }
 
+// What a handle holds, about: the slot arrays and the idle winner (24 bytes a
+// slot); excess, heights, lists and queues (a vertex); the mid-size levels'
+// segments and the counters.
+constexpr size_t HANDLE_SLOT_BYTES = 24, HANDLE_VERTEX_BYTES = 96, HANDLE_BYTES = 64u << 20;
+
 unsigned blocks_for(int64_t items, int per) { return (unsigned)std::max<int64_t>(1, (items + per - 1) / per); }
 
 // Pieces of one allocation.
@@ -311,8 +316,8 @@ struct Arena {
 
 mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, const int32_t* cap,
                              int32_t slack_min, int32_t slack_pct, hipStream_t st, const DeviceAllocator& mem,
-                             DeviceBiCSR* out, bool* no_scratch) {
-    *no_scratch = false;
+                             DeviceBiCSR* out, bool* no_room) {
+    *no_room = false;
     const int64_t count = 2 * m;
     int bits = 1;
     while ((1ll << bits) < n) ++bits;
@@ -342,12 +347,20 @@ mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int
     long long* mtile;
     BuildCounts* bc;
     carve(a, &in, key, val, &hist, &totals, &sum, &first, &end, &size, &start, &tile, &mtile, &bc);  // sizes only
-    // scratch of this call only, not the handle's: from the device itself, so
-    // that an allocator sized for the handle's buffers still suffices
+    // Scratch of this call only, not the handle's: from the device itself, so
+    // that an allocator sized for the handle's buffers still suffices.  The
+    // slot arrays are allocated beside it, so it is taken only where it and
+    // the whole handle fit in half of the free memory (the other half is for
+    // what other threads load and repair meanwhile); elsewhere the host
+    // builder needs none.  (The query takes 5 us.)
+    const int64_t most_slots = std::min<int64_t>(count + n + (int64_t)n * slack_min + count / 100 * slack_pct, INT_MAX);
+    const size_t handle = HANDLE_SLOT_BYTES * (size_t)most_slots + HANDLE_VERTEX_BYTES * (size_t)n + HANDLE_BYTES;
+    size_t free_bytes = 0, total_bytes = 0;
     void* block = nullptr;
-    if (hipMalloc(&block, a.used) != hipSuccess) {
+    if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess || a.used + handle > free_bytes / 2 ||
+        hipMalloc(&block, a.used) != hipSuccess) {
         (void)hipGetLastError();
-        *no_scratch = true;
+        *no_room = true;
         return MF_ERR_OUT_OF_MEMORY;
     }
     a = Arena{(char*)block, 0};
@@ -397,8 +410,13 @@ mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int
     if (mem.allocate((void**)&out->a.cr, sizeof(int2) * (size_t)S) != hipSuccess ||
         mem.allocate((void**)&out->a.rev, 4 * (size_t)S) != hipSuccess ||
         mem.allocate((void**)&out->a.cap, 4 * (size_t)S) != hipSuccess ||
-        mem.allocate((void**)&out->a.capsum, 4 * (size_t)S) != hipSuccess)
+        mem.allocate((void**)&out->a.capsum, 4 * (size_t)S) != hipSuccess) {
+        // (another thread took the room meanwhile: once more without the
+        // scratch; a caller's allocator that refuses is taken at its word)
+        (void)hipGetLastError();
+        *no_room = !mem.alloc_fn;
         return MF_ERR_OUT_OF_MEMORY;
+    }
     k_build_row_ptr<<<blocks_for((int64_t)n + 1, BLOCK), BLOCK, 0, st>>>(n, start, out->row_ptr);
     k_build_slack<<<stride_blocks(8 * (int64_t)n, BLOCK), BLOCK, 0, st>>>(n, out->row_ptr, out->row_len, out->a);
     k_build_slots<<<blocks_for(c.entries, BLOCK), BLOCK, 0, st>>>(c.entries, bits, mkey, sum, first, end,

@@ -442,13 +442,13 @@ struct DeviceBiCSR {
     int64_t slots = 0, pairs = 0, m_unique = 0;
 };
 // The same graph as build_bicsr with res = cap, on the device; arguments
-// checked by bicsr_arguments_ok.  Same errors, MF_ERR_OUT_OF_MEMORY
-// (*no_scratch: for its scratch, about 76 bytes per edge taken with hipMalloc
-// for the call; the host builder needs none) and MF_ERR_DEVICE; the stream is
-// idle on return.
+// checked by bicsr_arguments_ok.  Same errors, MF_ERR_OUT_OF_MEMORY (*no_room:
+// the device has no room for its scratch, about 76 bytes per edge for the
+// length of the call, beside the handle; the host builder needs none) and
+// MF_ERR_DEVICE; the stream is idle on return.
 mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, const int32_t* cap,
                              int32_t slack_min, int32_t slack_pct, hipStream_t st, const DeviceAllocator& mem,
-                             DeviceBiCSR* out, bool* no_scratch);
+                             DeviceBiCSR* out, bool* no_room);
 
 // Device relayout (relayout.cpp): runs the plan, allocates the new slot
 // arrays, moves the slots and frees the old arrays; *arrays and *S_new then

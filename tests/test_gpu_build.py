@@ -108,3 +108,33 @@ def test_device_build_capacity_sums(device):
     with pytest.raises(mf.MFError) as ei:
         mf.MaxFlowGraph(1000, u, v, c, 0, 999)
     assert ei.value.status == mf.MF_ERR_OVERFLOW
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hook", [False, True])
+def test_load_where_scratch_and_slots_do_not_fit_together(device, hook):
+    """The device builder needs 76 bytes per edge beside the slot arrays.  With
+    room for either but not for both, the graph is built on the host instead,
+    also where the handle's memory comes from a caller's allocator."""
+    import torch
+    opt = dict(allocator=mf.TorchAllocator(device=0, stream=torch.cuda.current_stream())) if hook else {}
+    n, m, left = 500_000, 4_000_000, 480 << 20   # scratch 320 MB, slot arrays 240 MB, the whole handle 370 MB
+    u, v, c = _edges("random", n, m, 4)
+    _, _, slots, capacity, _ = _expect(n, u, v, c)
+    with mf.MaxFlowGraph(n, u, v, c, 0, n - 1) as G:
+        want = G.maxflow()
+    torch.cuda.empty_cache()
+    print(f"[test] load beside {left >> 20} MB of free memory", flush=True)
+    held = []
+    try:
+        while torch.cuda.mem_get_info()[0] > left + (20 << 20):
+            held.append(torch.empty(torch.cuda.mem_get_info()[0] - left, dtype=torch.uint8, device="cuda"))
+        with mf.MaxFlowGraph(n, u, v, c, 0, n - 1, **opt) as G:
+            st = G.stats()
+            assert (st["slots"], st["slot_capacity"]) == (slots, capacity)
+            held.clear()
+            torch.cuda.empty_cache()
+            assert G.maxflow() == want
+    finally:
+        held.clear()
+        torch.cuda.empty_cache()
