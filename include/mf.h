@@ -89,7 +89,11 @@ typedef struct mf_options {
      * alloc(bytes, alloc_ctx) and given back with free(ptr, alloc_ctx), e.g. a
      * framework's caching allocator (launch the handle on that framework's
      * stream then).  Both NULL (default): hipMalloc / hipFree.  Setting only
-     * one is MF_ERR_INVALID.  alloc returns NULL when it has no memory. */
+     * one is MF_ERR_INVALID.  alloc returns NULL when it has no memory.
+     * mf_graph_load of 4096 or more edges also uses scratch (76 bytes per edge)
+     * that is not the handle's: from the device's stream-ordered pool, given
+     * back before it returns, and only where it and the handle fit in half of
+     * the device's free memory (else the graph is built on the host). */
     void* (*alloc)(size_t bytes, void* ctx);
     void (*free)(void* ptr, void* ctx);
     void* alloc_ctx;

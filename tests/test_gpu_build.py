@@ -138,3 +138,32 @@ def test_load_where_scratch_and_slots_do_not_fit_together(device, hook):
     finally:
         held.clear()
         torch.cuda.empty_cache()
+
+
+@pytest.mark.gpu
+def test_load_waits_for_its_own_stream_only(device):
+    """A load returns while another stream's work still runs."""
+    import time
+    import torch
+    n, m = 2000, 20_000
+    u, v, c = _edges("random", n, m, 5)
+    mf.MaxFlowGraph(n, u, v, c, 0, n - 1).close()
+    beside = []
+    # two streams may share one of the hardware's queues, where a load waits
+    # for whatever is ahead of it: a few streams are tried
+    for attempt in range(6):
+        other, ev = torch.cuda.Stream(), torch.cuda.Event()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(other):
+            torch.cuda._sleep(300_000_000)
+            ev.record()
+        t = time.perf_counter()
+        G = mf.MaxFlowGraph(n, u, v, c, 0, n - 1)
+        beside.append(not ev.query())
+        print(f"[test] load beside a busy stream {1e3 * (time.perf_counter() - t):.1f} ms, beside it: {beside[-1]}",
+              flush=True)
+        torch.cuda.synchronize()
+        G.close()
+        if beside[-1]:
+            break
+    assert any(beside)
