@@ -1711,22 +1711,25 @@ mf_status mf_graph_load(int32_t n, int64_t m, const int32_t* src, const int32_t*
         delete g;
         return r;
     };
-    // no usable device: edges are validated all the same
-    auto no_device = [&]() {
-        mf_status r = on_device ? mf::build_bicsr(n, m, src, dst, cap, s, t, slack_min, slack_pct, &b) : MF_OK;
-        return fail(r != MF_OK ? r : MF_ERR_DEVICE);
+    // no usable device, or no memory there: what is wrong with the edges is
+    // the error all the same
+    auto unbuilt = [&](mf_status r) {
+        const mf_status edges =
+            on_device ? mf::build_bicsr(n, m, src, dst, cap, s, t, slack_min, slack_pct, &b) : MF_OK;
+        return fail(edges != MF_OK ? edges : r);
     };
     int dev = o.device;
-    if (dev < 0 && hipGetDevice(&dev) != hipSuccess) return no_device();
-    if (hipSetDevice(dev) != hipSuccess) return no_device();
+    if (dev < 0 && hipGetDevice(&dev) != hipSuccess) return unbuilt(MF_ERR_DEVICE);
+    if (hipSetDevice(dev) != hipSuccess) return unbuilt(MF_ERR_DEVICE);
     g->device = dev;
     if (o.stream) {
         g->stream = (hipStream_t)o.stream;
     } else {
-        if (hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking) != hipSuccess) return no_device();
+        if (hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking) != hipSuccess) return unbuilt(MF_ERR_DEVICE);
         g->own_stream = true;
     }
     rc = load_structure(g, on_device ? nullptr : &b, m, src, dst, cap);
+    if (rc == MF_ERR_OUT_OF_MEMORY || rc == MF_ERR_DEVICE) return unbuilt(rc);
     if (rc != MF_OK) return fail(rc);
     b = mf::HostBiCSR();
     apply_tuning(g, tuning);

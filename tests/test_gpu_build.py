@@ -167,3 +167,20 @@ def test_load_waits_for_its_own_stream_only(device):
         if beside[-1]:
             break
     assert any(beside)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what,status", [("invalid", mf.MF_ERR_INVALID), ("pair sum", mf.MF_ERR_OVERFLOW),
+                                         ("good", mf.MF_ERR_OUT_OF_MEMORY)])
+def test_edges_decide_the_error_before_memory_does(device, what, status):
+    u, v, c = _bad(4500, c=-1) if what == "invalid" else _edges("random", 1000, 9000, 3)
+    if what == "pair sum":
+        u[10:12], v[10:12], c[10:12] = (7, 9), (9, 7), INT_MAX
+
+    class Refuses:
+        alloc_fn = mf.ALLOC_FN(lambda nbytes, ctx: None)
+        free_fn = mf.FREE_FN(lambda ptr, ctx: None)
+
+    with pytest.raises(mf.MFError) as ei:
+        mf.MaxFlowGraph(1000, u, v, c, 0, 999, allocator=Refuses, device=0)
+    assert ei.value.status == status
