@@ -493,7 +493,8 @@ void apply_loop_options(mf_graph* g, const mf_options& o) {
     auto on = [](int32_t v, bool dflt) { return v > 0 ? true : v < 0 ? false : dflt; };
     g->first_chunk = o.bfs_first_chunk > 0 ? o.bfs_first_chunk : 7;
     g->narrow_max = o.bfs_narrow_slots < 0 ? 0 : o.bfs_narrow_slots > 0 ? o.bfs_narrow_slots : 4096;
-    if (g->narrow_lds == 0) g->narrow_max = 0;
+    // (to what the kernel takes, so that larger frontiers are left to the mid-size levels)
+    g->narrow_max = g->narrow_lds == 0 ? 0 : std::min(g->narrow_max, mf::narrow_limit(g->slot_cap));
     g->medium_max = o.bfs_medium_slots < 0 ? 0 : o.bfs_medium_slots > 0 ? o.bfs_medium_slots : 65536;
     g->medium_blocks = o.bfs_medium_blocks > 0 ? o.bfs_medium_blocks : 16;
     // mid-size frontiers need cooperative launch (every block resident)

@@ -89,3 +89,20 @@ def test_thin_levels_and_rounds(device, spec):
             assert oracle.cert_check(g.n, g.src, g.dst, g.cap, g.s, g.t, None, side, want)[0] == 0
             assert G.apply_batch(*batch) == after
             assert G.min_cut()[1] == after
+
+
+# Levels of 20,000 slots, between what one workgroup holds and the limits asked
+# for, are the mid-size levels' (bfs_alpha: no bottom-up level takes them).
+@pytest.mark.gpu
+@pytest.mark.parametrize("make_graph,narrow,launches", [
+    (lambda: ring_layers(5000, 2, 12, 63300), 65536, 0)])
+def test_levels_one_workgroup_refuses_run_mid_size(device, make_graph, narrow, launches):
+    g = make_graph()
+    h_want, _ = oracle.DynOracle(g.n, g.src, g.dst, g.cap, g.s, g.t).initial_labels()
+    print(f"[test] refused levels {g.name} n={g.n}", flush=True)
+    with mf.MaxFlowGraph(g.n, g.src, g.dst, g.cap, g.s, g.t, bfs_narrow_slots=narrow, bfs_alpha=-1) as G:
+        for _ in range(2):                       # the second starts from what the first left
+            G.profile(0xFF)                      # (counts afresh)
+            assert np.array_equal(G.initial_labels()[0], h_want)
+            assert G.stats()["kernel_launches"]["global_relabel"] <= launches
+        assert G.maxflow() == oracle.DynOracle(g.n, g.src, g.dst, g.cap, g.s, g.t).static()
