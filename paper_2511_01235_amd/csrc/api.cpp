@@ -662,10 +662,12 @@ mf_status global_relabel(mf_graph* g, const LoopMode& m, int64_t* levels_out, in
     bool medium = false;  // set when a read finds a mid-size frontier waiting
     const int64_t medium_cap = std::min<int64_t>(g->medium_max, m.L.mq.seg);
     const int medium_grid = std::min<int>(g->medium_blocks, m.L.mq_blocks);
+    const int pieces = narrow_max > 0 ? mf::narrow_pieces(g->narrow_lds, m.L.bits.nwords) : 0;
+    auto thin = [&](unsigned long long front) { return narrow_max > 0 && mf::narrow_takes(front, narrow_max, pieces); };
     auto mid_size = [&](int lv) {
-        const int64_t slots = (int64_t)(m.L.ctr_h->front[lv % 3] >> 32);
-        return medium_grid > 0 && m.L.mq.q && !g->coop_broken && !g->trace_gr && slots > narrow_max &&
-               slots <= medium_cap;
+        const unsigned long long front = m.L.ctr_h->front[lv % 3];
+        return medium_grid > 0 && m.L.mq.q && !g->coop_broken && !g->trace_gr && !thin(front) &&
+               (int64_t)(front >> 32) <= medium_cap;
     };
     auto t_last = std::chrono::steady_clock::now();
     if (g->trace_gr) {
@@ -686,8 +688,7 @@ mf_status global_relabel(mf_graph* g, const LoopMode& m, int64_t* levels_out, in
             if (rc != MF_OK) return rc;
             const int level_before = level;
             level = m.L.ctr_h->levels;
-            if (level_before == 0 && main)
-                g->narrow_seed = (int64_t)(m.L.ctr_h->seed_front >> 32) <= narrow_max;
+            if (level_before == 0 && main) g->narrow_seed = thin(m.L.ctr_h->seed_front);
             const int cnt = (int)(unsigned)(m.L.ctr_h->front[level % 3] & 0xFFFFFFFFull);
             if (cnt == 0) break;
             if (level > g->n + 2) {
@@ -749,7 +750,7 @@ mf_status global_relabel(mf_graph* g, const LoopMode& m, int64_t* levels_out, in
         mf_status rc = read_lane(g, m.L);
         if (rc != MF_OK) return rc;
         // seeds of the next relabel: like this one's, as its level 0 recorded them
-        if (main) g->narrow_seed = (int64_t)(m.L.ctr_h->seed_front >> 32) <= narrow_max;
+        if (main) g->narrow_seed = thin(m.L.ctr_h->seed_front);
         const int cnt = (int)(unsigned)(m.L.ctr_h->front[level % 3] & 0xFFFFFFFFull);
         if (g->trace_gr) {
             // the level just done: its frontier, the unvisited slots before it,
@@ -776,7 +777,7 @@ mf_status global_relabel(mf_graph* g, const LoopMode& m, int64_t* levels_out, in
         }
         if (g->trace_gr) continue;  // one level per launch
         chunk = std::min(chunk * 2, 64);
-        narrow = narrow_max > 0 && (int64_t)(m.L.ctr_h->front[level % 3] >> 32) <= narrow_max;
+        narrow = thin(m.L.ctr_h->front[level % 3]);
         medium = !narrow && mid_size(level);
     }
     *levels_out += level;

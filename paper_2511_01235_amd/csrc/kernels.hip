@@ -1118,7 +1118,7 @@ __device__ __forceinline__ void lds_barrier() {
 // the current one before multi-block levels continue.
 constexpr int NARROW_BLOCK = 1024;
 constexpr int NARROW_SCAN = 768;         // threads that scan; the others write heights
-constexpr int NP = 4;                    // slots of a piece, and lanes that scan it
+constexpr int NP = NARROW_PIECE;         // slots of a piece, and lanes that scan it
 constexpr int NARROW_CAP = 4096;         // pieces of a frontier, at most
 constexpr int NARROW_CAP_MIN = 1536;     // ... with the bitmap in LDS, at least
 constexpr int NARROW_MAX = 8192;         // slots of a frontier
@@ -1309,8 +1309,7 @@ __global__ void __launch_bounds__(NARROW_BLOCK) k_gr_narrow(DevGraph g, int lv0,
     int lab = cap ? excess_labelled(ctr, lv0) : 0;
     const int total = cap ? excess_total(ctr) : INT_MAX;
     if (tid == 0 && lv0 == 0) ctr->seed_front = front0;
-    // (pieces: at most one short one per queue entry)
-    if (cnt0 == 0 || (long long)(front0 >> 32) > max_slots || (front0 >> 32) / NP + (unsigned)cnt0 > (unsigned)pieces) {
+    if (cnt0 == 0 || !narrow_takes(front0, max_slots, pieces)) {
         if (tid == 0) ctr->levels = lv0;
         return;
     }
@@ -3806,14 +3805,21 @@ int narrow_lds_bytes(int device) {
     return bytes;
 }
 
+// pieces in each of two lists beside the visited bitmap in LDS
+static int64_t narrow_room(int lds_bytes, int nwords) { return (lds_bytes - 4 * (int64_t)nwords) / 16; }
+
+// (the bitmap goes to LDS where it leaves room for NARROW_CAP_MIN)
+int narrow_pieces(int lds_bytes, int nwords) {
+    const int64_t room = narrow_room(lds_bytes, nwords);
+    return (int)std::min<int64_t>(room >= NARROW_CAP_MIN ? room : NARROW_CAP, NARROW_CAP);
+}
+
 int64_t narrow_limit(int64_t slots) { return slots < NARROW_SLOTS ? NARROW_MAX : 0; }
 
 void launch_gr_narrow(const DevGraph& g, int lv0, int2* q0, int2* q1, DevCounters* ctr, const GrBits& bits,
                       long long max_slots, int lds_bytes, bool forward, hipStream_t st) {
-    // the visited bitmap in LDS where it leaves room for two lists of pieces
-    const int64_t room = (lds_bytes - 4 * (int64_t)bits.nwords) / 16;
-    const bool lbm = room >= NARROW_CAP_MIN;
-    const int pieces = (int)std::min<int64_t>(lbm ? room : NARROW_CAP, NARROW_CAP);
+    const bool lbm = narrow_room(lds_bytes, bits.nwords) >= NARROW_CAP_MIN;
+    const int pieces = narrow_pieces(lds_bytes, bits.nwords);
     const size_t shm = 16 * (size_t)pieces + (lbm ? 4 * (size_t)bits.nwords : 0);
     auto fn = forward ? (lbm ? k_gr_narrow<true, true> : k_gr_narrow<true, false>)
                       : (lbm ? k_gr_narrow<false, true> : k_gr_narrow<false, false>);

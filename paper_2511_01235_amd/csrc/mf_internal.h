@@ -330,6 +330,17 @@ void launch_gr_narrow(const DevGraph& g, int lv0, int2* q0, int2* q1, DevCounter
 int narrow_lds_bytes(int device);
 // the largest frontier they take in a graph of this many slots (0: never launch them)
 int64_t narrow_limit(int64_t slots);
+// the pieces of NARROW_PIECE slots that they hold of a frontier
+int narrow_pieces(int lds_bytes, int nwords);
+constexpr int NARROW_PIECE = 4;
+// Whether they take a frontier (a front[] word: slots and queue entries).  Its
+// rows have to fit as pieces, of which each entry may leave one short.  The
+// host and the kernel decide by this one rule: a frontier that the kernel
+// refuses goes to the mid-size levels, not to a launch that refuses it again.
+constexpr bool narrow_takes(unsigned long long front, int64_t max_slots, int pieces) {
+    const int64_t slots = (int64_t)(front >> 32), entries = (int64_t)(front & 0xFFFFFFFFull);
+    return slots <= max_slots && (slots + (NARROW_PIECE - 1) * entries) / NARROW_PIECE <= pieces;
+}
 // BFS levels from lv0 in one cooperative launch of `grid` 1024-thread blocks
 // while the frontier covers at most max_slots slots (ctr->levels: where to
 // continue; ctr->bar_err set if a grid barrier gave up)

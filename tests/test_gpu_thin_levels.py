@@ -91,11 +91,29 @@ def test_thin_levels_and_rounds(device, spec):
             assert G.min_cut()[1] == after
 
 
-# Levels of 20,000 slots, between what one workgroup holds and the limits asked
-# for, are the mid-size levels' (bfs_alpha: no bottom-up level takes them).
+def funnel(width, layers, wide, seed):
+    """s -> layers of `width` vertices, one to one -> `wide` vertices -> t: a
+    BFS from t meets the wide layer first and the thin ones behind it."""
+    rng = gen.rng_for(seed)
+    a = np.arange(width)
+    last = 1 + (layers - 1) * width
+    first_wide = 1 + layers * width
+    n = first_wide + wide + 1
+    w = first_wide + np.arange(wide)
+    u = [np.zeros(width, np.int64)] + [1 + i * width + a for i in range(layers - 1)] + [last + np.arange(wide) % width, w]
+    v = [1 + a] + [1 + (i + 1) * width + a for i in range(layers - 1)] + [w, np.full(wide, n - 1)]
+    u, v = np.concatenate(u), np.concatenate(v)
+    c = rng.integers(1, 30, u.size)
+    return gen.Graph(f"funnel_{width}_{wide}", n, u.astype(np.int32), v.astype(np.int32), c.astype(np.int32), 0, n - 1)
+
+
+# Levels of 3600 rows of two slots come back from the multi-block levels: up to
+# 8192 slots, but more pieces than one workgroup may have to hold (4096).  And
+# levels of 20,000 slots, between what one workgroup holds and the limits asked
+# for.  Both are the mid-size levels' (bfs_alpha: no bottom-up level takes them).
 @pytest.mark.gpu
 @pytest.mark.parametrize("make_graph,narrow,launches", [
-    (lambda: ring_layers(5000, 2, 12, 63300), 65536, 0)])
+    (lambda: funnel(3600, 40, 40_000, 63200), 8192, 7), (lambda: ring_layers(5000, 2, 12, 63300), 65536, 0)])
 def test_levels_one_workgroup_refuses_run_mid_size(device, make_graph, narrow, launches):
     g = make_graph()
     h_want, _ = oracle.DynOracle(g.n, g.src, g.dst, g.cap, g.s, g.t).initial_labels()
