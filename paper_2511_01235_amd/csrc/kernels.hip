@@ -186,9 +186,8 @@ __device__ __forceinline__ long long wave_excl_scan64(long long x, long long* to
     return (long long)v - x;
 }
 
-// The same over groups of G consecutive lanes (4, 8, 16 or the wave), for
-// rows that a group of lanes takes together.  Every lane of the wave calls
-// them.
+// The same over groups of G consecutive lanes (four or the wave), for rows
+// that a group of lanes takes together.  Every lane of the wave calls them.
 template <int CTRL>
 __device__ __forceinline__ unsigned long long dpp_move(unsigned long long x) {
     const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xF, 0xF, false);
@@ -197,14 +196,13 @@ __device__ __forceinline__ unsigned long long dpp_move(unsigned long long x) {
 }
 template <int G>
 __device__ __forceinline__ unsigned long long group_min(unsigned long long x) {
+    static_assert(G == 4 || G == WAVE, "quad permutations, or the whole wave");
     if constexpr (G == WAVE) {
         return wave_min_u64(x);
     } else {
         unsigned long long y;
-        y = dpp_move<0xB1>(x), x = y < x ? y : x;                            // the other lane of each pair
-        y = dpp_move<0x4E>(x), x = y < x ? y : x;                            // the other pair of the quad
-        if constexpr (G >= 8) y = dpp_move<0x141>(x), x = y < x ? y : x;     // the other quad of the eight
-        if constexpr (G >= 16) y = dpp_move<0x140>(x), x = y < x ? y : x;    // the other eight of the row
+        y = dpp_move<0xB1>(x), x = y < x ? y : x;  // the other lane of each pair
+        y = dpp_move<0x4E>(x), x = y < x ? y : x;  // the other pair of the quad
         return x;
     }
 }
@@ -223,8 +221,6 @@ __device__ __forceinline__ long long group_sum(long long x0) {
     } else {
         x += dpp_move<0xB1>(x);
         x += dpp_move<0x4E>(x);
-        if constexpr (G >= 8) x += dpp_move<0x141>(x);
-        if constexpr (G >= 16) x += dpp_move<0x140>(x);
         return (long long)x;
     }
 }
@@ -238,8 +234,6 @@ __device__ __forceinline__ long long group_excl_scan(long long x0, int sub) {
         unsigned long long y;
         y = dpp_move<0x111>(x), x += sub >= 1 ? y : 0ull;
         y = dpp_move<0x112>(x), x += sub >= 2 ? y : 0ull;
-        if constexpr (G >= 8) y = dpp_move<0x114>(x), x += sub >= 4 ? y : 0ull;
-        if constexpr (G >= 16) y = dpp_move<0x118>(x), x += sub >= 8 ? y : 0ull;
     }
     return (long long)x - x0;
 }
@@ -715,7 +709,6 @@ __device__ __forceinline__ void gr_level_body(const Par& P, const DevGraph& g, i
                                               int2* qout, DevCounters* ctr, const GrBits& bits,
                                               bool bu, bool bu_lb, bool bu_wide, const unsigned* s_bm,
                                               int cls = KC_GR) {
-    __shared__ int s_u[BS];
     __shared__ int s_beg[BS];
     __shared__ int s_pre[BS + 1];
     __shared__ int s_wsum[BS / WAVE];
@@ -924,7 +917,6 @@ __device__ __forceinline__ void gr_level_body(const Par& P, const DevGraph& g, i
             if (tid < per && idx < cnt) {
                 int2 ent = qin[idx];
                 int rl = g.row_len[ent.x];
-                s_u[tid] = ent.x;
                 s_beg[tid] = g.row_ptr[ent.x] + ent.y;
                 len = min(rl - ent.y, GR_CHUNK);
                 exam += 3;
