@@ -29,6 +29,7 @@
 #include <climits>
 #include <cstdint>
 #include <cstdlib>
+#include <initializer_list>
 
 #include "mf.h"
 #include "mf_internal.h"
@@ -3748,6 +3749,17 @@ void launch_gr_init(const DevGraph& g, int2* q0, DevCounters* ctr, const GrBits&
     k_gr_init<<<grid_for(g.n, 256, 8192), 256, 0, st>>>(g, q0, ctr, bits, seed_deficits);
 }
 
+// Dynamic LDS for each of the kernels; false (and no error left for the next
+// launch check to find) where the device refuses it.
+static bool allow_lds(std::initializer_list<const void*> kernels, int bytes) {
+    for (const void* k : kernels)
+        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+    return true;
+}
+
 int gr_level_lds_bytes(int nwords, int device) {
     int max_lds = 0;
     if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess)
@@ -3756,12 +3768,11 @@ int gr_level_lds_bytes(int nwords, int device) {
     // the level kernel's own LDS (entry staging, prefix sums, deferred rows) comes on top
     const int static_bytes = 4 * (4 * GRL_BLOCK_LDS + 1 + GRL_BLOCK_LDS / WAVE + 1) + 64;
     if (bytes + static_bytes > max_lds) return 0;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gr_level<false, GRL_BLOCK_LDS>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gr_level<true, GRL_BLOCK_LDS>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess)
-        return 0;
-    return bytes;
+    return allow_lds({reinterpret_cast<const void*>(&k_gr_level<false, GRL_BLOCK_LDS>),
+                      reinterpret_cast<const void*>(&k_gr_level<true, GRL_BLOCK_LDS>)},
+                     bytes)
+               ? bytes
+               : 0;
 }
 
 // grid: blocks of the 256-thread variant; the LDS variant runs one block per
@@ -3788,13 +3799,13 @@ int narrow_lds_bytes(int device) {
     if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess) return 0;
     const int bytes = max_lds - NARROW_STATIC;
     if (bytes < 16 * NARROW_CAP) return 0;
-    const void* fns[] = {reinterpret_cast<const void*>(&k_gr_narrow<false, false>),
-                         reinterpret_cast<const void*>(&k_gr_narrow<false, true>),
-                         reinterpret_cast<const void*>(&k_gr_narrow<true, false>),
-                         reinterpret_cast<const void*>(&k_gr_narrow<true, true>)};
-    for (const void* f : fns)
-        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return 0;
-    return bytes;
+    return allow_lds({reinterpret_cast<const void*>(&k_gr_narrow<false, false>),
+                      reinterpret_cast<const void*>(&k_gr_narrow<false, true>),
+                      reinterpret_cast<const void*>(&k_gr_narrow<true, false>),
+                      reinterpret_cast<const void*>(&k_gr_narrow<true, true>)},
+                     bytes)
+               ? bytes
+               : 0;
 }
 
 // pieces in each of two lists beside the visited bitmap in LDS
@@ -4020,11 +4031,11 @@ int rounds_narrow_lds_bytes(int device) {
     if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess) return 0;
     const int bytes = max_lds - RN_STATIC;
     if (bytes < RN_LISTS) return 0;
-    const void* fns[] = {reinterpret_cast<const void*>(&k_rounds_narrow<false>),
-                         reinterpret_cast<const void*>(&k_rounds_narrow<true>)};
-    for (const void* f : fns)
-        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return 0;
-    return bytes;
+    return allow_lds({reinterpret_cast<const void*>(&k_rounds_narrow<false>),
+                      reinterpret_cast<const void*>(&k_rounds_narrow<true>)},
+                     bytes)
+               ? bytes
+               : 0;
 }
 
 int rounds_narrow_max() { return RN_MAX; }

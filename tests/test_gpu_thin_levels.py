@@ -124,3 +124,19 @@ def test_levels_one_workgroup_refuses_run_mid_size(device, make_graph, narrow, l
             assert np.array_equal(G.initial_labels()[0], h_want)
             assert G.stats()["kernel_launches"]["global_relabel"] <= launches
         assert G.maxflow() == oracle.DynOracle(g.n, g.src, g.dst, g.cap, g.s, g.t).static()
+
+
+@pytest.mark.gpu
+def test_bitmap_that_does_not_fit_in_lds_is_left_out(device):
+    """bfs_lds_bitmap at a size where the device refuses that much LDS beside
+    the level kernel's own: the graph loads, without the copy."""
+    n, m = 1_160_000, 6000
+    rng = gen.rng_for(63400)
+    u = rng.integers(0, n, m)
+    v = (u + 1 + rng.integers(0, n - 1, m)) % n
+    u[:2], v[:2] = (0, 7), (7, n - 1)
+    c = rng.integers(1, 50, m)
+    e = [x.astype(np.int32) for x in (u, v, c)]
+    want = oracle.DynOracle(n, *e, 0, n - 1).static()
+    with mf.MaxFlowGraph(n, *e, 0, n - 1, bfs_lds_bitmap=1) as G:
+        assert want > 0 and G.maxflow() == want
