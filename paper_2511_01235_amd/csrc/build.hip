@@ -416,7 +416,6 @@ mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int
         mem.allocate((void**)&out->a.capsum, 4 * (size_t)S) != hipSuccess) {
         // (another thread took the room meanwhile: once more without the
         // scratch; a caller's allocator that refuses is taken at its word)
-        (void)hipGetLastError();
         *no_room = !mem.alloc_fn;
         return MF_ERR_OUT_OF_MEMORY;
     }

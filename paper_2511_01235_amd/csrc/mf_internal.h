@@ -236,9 +236,11 @@ struct DeviceAllocator {
     void (*free_fn)(void*, void*) = nullptr;
     void* ctx = nullptr;
     hipError_t allocate(void** p, size_t bytes) const {
-        if (!alloc_fn) return hipMalloc(p, bytes);
-        *p = alloc_fn(bytes, ctx);
-        return *p ? hipSuccess : hipErrorOutOfMemory;
+        hipError_t e = hipSuccess;
+        if (!alloc_fn) e = hipMalloc(p, bytes);
+        else if (!(*p = alloc_fn(bytes, ctx))) e = hipErrorOutOfMemory;
+        if (e != hipSuccess) (void)hipGetLastError();  // not for the next launch check to find
+        return e;
     }
     void release(void* p) const {
         if (!p) return;

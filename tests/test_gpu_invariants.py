@@ -172,3 +172,28 @@ def test_iteration_cap_not_converged():
         G.tune(max_iterations=0)
         assert G.maxflow() == o.static()
         assert G.apply_batch(u, v, c) == o.apply(u, v, c)
+
+
+def test_refused_load_leaves_other_handles_alone():
+    """A load that the device has no memory for is out of memory; the next call
+    on another handle finds nothing of it."""
+    import torch
+    g, stream, k, _ = gen.workload("er2000")
+    o = oracle.DynOracle(g.n, g.src, g.dst, g.cap, g.s, g.t)
+    n, left = 40_000_000, 1 << 30                # 100 bytes a vertex
+    print(f"[test] refused load beside {left >> 20} MB of free memory", flush=True)
+    held = []
+    with mf.MaxFlowGraph(g.n, g.src, g.dst, g.cap, g.s, g.t) as G:
+        assert G.maxflow() == o.static()
+        torch.cuda.empty_cache()
+        try:
+            while torch.cuda.mem_get_info()[0] > left + (20 << 20):
+                held.append(torch.empty(torch.cuda.mem_get_info()[0] - left, dtype=torch.uint8, device="cuda"))
+            with pytest.raises(mf.MFError) as ei:
+                mf.MaxFlowGraph(n, np.array([0], np.int32), np.array([1], np.int32), np.array([1], np.int32), 0, 1)
+            assert ei.value.status == mf.MF_ERR_OUT_OF_MEMORY
+        finally:
+            held.clear()
+            torch.cuda.empty_cache()
+        b = stream.next_batch(k)
+        assert G.apply_batch(*b) == o.apply(*b)
