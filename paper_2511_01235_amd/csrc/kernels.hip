@@ -594,8 +594,9 @@ __device__ __forceinline__ void gr_init_body(const Par& P, const DevGraph& g, in
         // slots of every row that may be labelled, the seeds' included
         ctr->unv[2] = (g.nslots ? *g.nslots : (long long)g.used_slots) - g.row_len[g.pinned];
         // per vertex: height, excess; a capped relabel also reads the old
-        // height and keeps it in h_prev
-        add_bytes(g, cls, (cap_ok ? 20ull : 12ull) * (unsigned long long)N);
+        // height and keeps it in h_prev; the bitmaps' words
+        add_bytes(g, cls, (cap_ok ? 20ull : 12ull) * (unsigned long long)N +
+                              (WORDS ? 4ull * GR_BITMAPS * (unsigned long long)bits.nwords : 0ull));
     }
 }
 
@@ -987,10 +988,10 @@ __device__ __forceinline__ void gr_level_body(const Par& P, const DevGraph& g, i
     // per scanned slot: col+res (8), capsum (4), plus h[col] (4) without the
     // LDS bitmap; per staged entry or unlabelled vertex its words; per
     // discovered vertex the CAS, two bitmap words and its queue entry, and
-    // with a capped relabel its excess (8)
+    // with a capped relabel its word of the excess bitmap (4)
     unsigned long long per_slot = (s_bm ? 12ull : 16ull) - ((bu && !FWD) ? 4ull : 0ull);
     if (g.count_bytes) {
-        const unsigned long long per_found = g.bfs_cap ? 32ull : 24ull;
+        const unsigned long long per_found = g.bfs_cap ? 28ull : 24ull;
         unsigned long long b = wave_sum_u64(per_slot * scanned + 4ull * exam + per_found * found);
         if (lane == 0) add_bytes(g, cls, b);
     }
@@ -1093,14 +1094,15 @@ __device__ __forceinline__ void lds_barrier() {
 // to read, no prefix sum, no search), and with LBM the visited bitmap,
 // claimed there instead of by a global atomic.  What is left of the chain is
 // a slot's {col, res, capsum} and then the labelled vertex's row bounds and
-// excess: two trips to memory a level.  Stores complete in half a microsecond
+// excess bit: two trips to memory a level.  Stores complete in half a microsecond
 // and a wave's later loads count as done only after its earlier stores, so
 // the waves that scan store nothing: the last waves of the workgroup write
 // the heights of the vertices labelled one level before, and the barrier
-// between levels waits for LDS only.  Measured on a 256 x 256 grid, per
-// level: 6.8 us with queue and counters in memory (nine trips, five barriers
-// that drained stores), 2.3 with a map of single slots in LDS, 1.8 with
-// pieces.
+// between levels waits for LDS only.  Measured, launch time over levels:
+// repairs of a 256-wide grid 8.2 us with queue and counters in memory (nine
+// trips, five barriers that drained stores) and 2.2 now, the solve of a
+// 301-wide one 6.1 and 1.75; a map of single slots instead of pieces took
+// half a microsecond more.
 //
 // LBM needs the bitmap beside the pieces in LDS (the host checks).  Without
 // it a vertex is claimed by a CAS on its height after a test of its visited
@@ -1113,7 +1115,13 @@ constexpr int NARROW_BLOCK = 1024;
 constexpr int NARROW_SCAN = 768;         // threads that scan; the others write heights
 constexpr int NP = NARROW_PIECE;         // slots of a piece, and lanes that scan it
 constexpr int NARROW_CAP = 4096;         // pieces of a frontier, at most
-constexpr int NARROW_CAP_MIN = 1536;     // ... with the bitmap in LDS, at least
+// ... with the bitmap in LDS, at least: above 785,000 vertices the bitmap
+// leaves room for fewer pieces than without it, down to these at 1.11 million.
+// Repairs with the bitmap left out there (and 4096 pieces) against this: grids
+// of width 900, 1024 and 1050 61.7, 64.7 and 50.6 ms against 48.7, 62.3 and
+// 47.2; RMAT and ER graphs of 0.8 to 1.1 million vertices the same within
+// their spread.
+constexpr int NARROW_CAP_MIN = 1536;
 constexpr int NARROW_MAX = 8192;         // slots of a frontier
 constexpr int NARROW_STATIC = 128;       // the kernel's other LDS
 constexpr int64_t NARROW_SLOTS = 1ll << 29;  // graphs with more slots are not taken (a piece's first slot has 29 bits)
@@ -1405,9 +1413,13 @@ __global__ void __launch_bounds__(NARROW_BLOCK) k_gr_narrow(DevGraph g, int lv0,
         ctr->levels = lv;
     }
     if (g.count_bytes) {
-        // per slot: col + res (8), capsum (4), the visited word (4); per
-        // labelled vertex its height, row bounds and excess
-        const unsigned long long b = wave_sum_u64((tid == 0 ? 16ull * scanned : 0ull) + 24ull * found);
+        // per slot: col + res (8), backward its capsum (4), without LBM the
+        // visited word (4); per labelled vertex its height and row bounds
+        // (12), with a capped relabel its word of the excess bitmap (4),
+        // without LBM its visited word again (4)
+        constexpr unsigned long long per_slot = 8ull + (FWD ? 0ull : 4ull) + (LBM ? 0ull : 4ull);
+        const unsigned long long per_found = 12ull + (cap ? 4ull : 0ull) + (LBM ? 0ull : 4ull);
+        const unsigned long long b = wave_sum_u64((tid == 0 ? per_slot * scanned : 0ull) + per_found * found);
         if (lane_id() == 0) add_bytes(g, KC_GRS, b);
     }
 }
@@ -1825,8 +1837,9 @@ __global__ void __launch_bounds__(GRM_BLOCK) k_gr_medium(DevGraph g, int lv0, in
     if (g.count_bytes) {
         // per scanned slot: col+res (8), capsum (4), the visited word (4);
         // per staged entry its 16 bytes; per labelled vertex the CAS, its row
-        // bounds, excess, bitmap word and entry
-        const unsigned long long b = wave_sum_u64(16ull * scanned + 16ull * staged + 40ull * found);
+        // bounds, bitmap word and entry, with a capped relabel its word of the
+        // excess bitmap
+        const unsigned long long b = wave_sum_u64(16ull * scanned + 16ull * staged + (cap ? 36ull : 32ull) * found);
         if (lane == 0) add_bytes(g, KC_GRS, b);
     }
 }
@@ -2056,8 +2069,11 @@ constexpr int PR_UNROLL_BLOCK = 4;
 // gather and the pushes.  The vertex is left when its excess is gone; what
 // arrives later puts it on the next worklist.  (A thread per row with a
 // reload per slot and a poll of e(u) for every cycle left took 39 us a launch
-// in a solve of RMAT-18, this 18.)  valid: whether this lane's group has a vertex; every lane of the
-// wave calls it.  *raised: h(u) went up.
+// in a solve of RMAT-18, this 18.  The row's registers cost occupancy:
+// k_pr_small has 82 VGPRs for 48, five waves per SIMD for seven, and the
+// 1024-thread batch kernels spill 36 and 180 bytes a lane for 0 and 80.)
+// valid: whether this lane's group has a vertex; every lane of the wave calls
+// it.  *raised: h(u) went up.
 template <bool PULL, int G, int SL, class Act>
 __device__ __forceinline__ unsigned long long pr_group(const DevGraph& g, const Act& act, int u, bool valid, int kc,
                                                        bool* raised) {
@@ -3338,10 +3354,11 @@ __global__ void __launch_bounds__(256) k_value_if_empty(DevGraph g, DevCounters*
 // A round is bound by its chain of trips to memory and by the barriers that
 // must see the pushes done; the lists, the activations and (LBM) the bit per
 // vertex that keeps a list free of repeats stay in LDS, and only the state of
-// the graph is in memory.  Measured on a 256 x 256 grid: 12 us a round before
-// (lists and repeat marks in memory, a thread per row, every row checked for
-// steep slots), 7.5 now.  Without LBM (more vertices than bits in LDS) the
-// repeats are found with mark[v] == epoch.
+// the graph is in memory.  Measured, launch time over rounds: repairs of a
+// 256-wide grid 14.0 us before (lists and repeat marks in memory, a thread per
+// row, every row checked for steep slots) and 9.2 now, the solve of a 301-wide
+// one, with longer lists, 23.4 and 17.0.  Without LBM (more vertices than bits
+// in LDS) the repeats are found with mark[v] == epoch.
 //
 // Lists alternate between two halves of LDS; input in a0, a1 with counts in
 // ctr->wl; on exit the list to run next is there too, its counts in
@@ -3745,7 +3762,7 @@ void launch_zero_loop_counters(DevCounters* ctr, hipStream_t st) {
 void launch_gr_init(const DevGraph& g, int2* q0, DevCounters* ctr, const GrBits& bits, int seed_deficits,
                     hipStream_t st) {
     k_zero_counters_front<<<1, 64, 0, st>>>(ctr);
-    // k_gr_init writes the four bitmaps whole (no clearing launch)
+    // k_gr_init writes the five bitmaps whole (no clearing launch)
     k_gr_init<<<grid_for(g.n, 256, 8192), 256, 0, st>>>(g, q0, ctr, bits, seed_deficits);
 }
 

@@ -37,7 +37,7 @@ struct DevGraph {
                                          // read instead (a captured launch keeps its arguments)
     unsigned long long* bytes_part;      // KC_NCLASS x BYTES_SLOTS algorithmic-byte partial sums
     int count_bytes;                     // 1 while kernel classes are being profiled
-    int bin0_max, bin1_max;              // worklist degree bins: thread up to bin0_max slots, wave up to bin1_max
+    int bin0_max, bin1_max;              // worklist degree bins: four lanes up to bin0_max slots, wave up to bin1_max
     const uint8_t* side;                 // not null: a relabel only labels vertices with side[v] == side_keep
     int side_keep;
     int32_t* act;                        // not null: push-relabel / remove-invalid-edges append every vertex
@@ -444,9 +444,10 @@ bool bicsr_arguments_ok(int32_t n, int64_t m, const int32_t* src, const int32_t*
 
 // ---- device Bi-CSR builder (build.hip) -----------------------------------
 // Edge counts it takes.  Below the minimum the host builder is no slower than
-// the thirty launches and two read-backs (whole loads of 2,000 / 4,000 /
-// 16,000 edges on the host: 0.31 / 0.40 / 1.08 ms; 16,000 on the device: 0.35);
-// above the maximum the entries would not fit 32-bit indices.
+// the thirty launches and two read-backs (whole loads of 4,096 / 8,000 /
+// 16,000 edges on the host: 0.36 / 0.55 / 0.91 ms, on the device 0.36 / 0.38 /
+// 0.39; 2,000 on the host 0.26); above the maximum the entries would not fit
+// 32-bit indices.
 constexpr int64_t BUILD_DEVICE_MIN = 4096;
 constexpr int64_t BUILD_DEVICE_MAX = 1ll << 30;
 struct DeviceBiCSR {
