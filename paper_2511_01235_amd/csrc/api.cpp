@@ -109,6 +109,7 @@ struct mf_graph {
     bool graph_capture = false;      // pipelined iterations replayed from a captured HIP graph
     bool capture_failed = false;     // capture or instantiation failed once: launch kernel by kernel
     bool no_capture = false;         // this call instantiates no new graph (allocation-free entry point)
+    bool long_rows = true;           // the last cut, or the load, saw a row of more than CUT_LONG slots
     bool heights_exact = true;       // heights are the last relabel's BFS distances (else a valid labelling
                                      // left by the round that ended the solve)
     hipStream_t cap_stream = nullptr;  // stream the iteration is captured on (never launched on)
@@ -395,6 +396,7 @@ mf_status upload_structure(mf_graph* g, const mf::HostBiCSR& b) {
     MF_HIP(hipStreamSynchronize(st));  // host vectors die on return
     g->pairs = b.pairs;
     g->m_unique = b.m_unique;
+    g->long_rows = std::any_of(b.row_len.begin(), b.row_len.end(), [](int32_t len) { return len > mf::CUT_LONG; });
     return MF_OK;
 }
 
@@ -431,6 +433,7 @@ mf_status load_structure(mf_graph* g, mf::HostBiCSR* host, int64_t m, const int3
     if (rc != MF_OK) return rc;
     g->pairs = b.pairs;
     g->m_unique = b.m_unique;
+    g->long_rows = b.long_rows;
     return slot_scratch(g, b.slots);
 }
 
@@ -1941,13 +1944,22 @@ mf_status mf_min_cut(mf_graph* g, uint8_t* source_side, int64_t* cut_capacity) {
         if (rc != MF_OK) return rc;
         g->heights_exact = true;
     }
+    const bool expected = g->long_rows;
     mf::launch_cut(g->dg, g->side, g->cut_acc, g->wl[0], st);
+    if (expected) mf::launch_cut_long(g->dg, g->cut_acc, g->wl[0], st);
     MF_HIP(hipGetLastError());
-    unsigned long long c = 0;
-    MF_HIP(hipMemcpyAsync(&c, g->cut_acc, sizeof(c), hipMemcpyDeviceToHost, st));
+    unsigned long long c[2] = {0, 0};  // the capacity, the rows on the list
+    MF_HIP(hipMemcpyAsync(c, g->cut_acc, sizeof(c), hipMemcpyDeviceToHost, st));
     if (source_side) MF_HIP(hipMemcpyAsync(source_side, g->side, (size_t)g->n, hipMemcpyDeviceToHost, st));
     MF_HIP(hipStreamSynchronize(st));
-    *cut_capacity = (int64_t)c;
+    g->long_rows = (int32_t)c[1] > 0;
+    if (g->long_rows && !expected) {  // rows have grown past the limit since
+        mf::launch_cut_long(g->dg, g->cut_acc, g->wl[0], st);
+        MF_HIP(hipGetLastError());
+        MF_HIP(hipMemcpyAsync(c, g->cut_acc, sizeof(c), hipMemcpyDeviceToHost, st));
+        MF_HIP(hipStreamSynchronize(st));
+    }
+    *cut_capacity = (int64_t)c[0];
     return MF_OK;
 }
 

@@ -39,6 +39,8 @@ constexpr int DIGITS = 256;
 struct BuildCounts {
     int invalid;                      // an edge out of range, u == v or c < 0
     int overflow;                     // c(u,v) + c(v,u) of a merged pair above int32
+    int long_rows;                    // a row of more than CUT_LONG slots
+    int pad;
     long long entries;                // merged entries (slots in use)
     unsigned long long with_capacity; // ... with capacity > 0
 };
@@ -235,10 +237,11 @@ __global__ void __launch_bounds__(BLOCK) k_merge(const unsigned long long* key, 
 
 __global__ void __launch_bounds__(BLOCK) k_build_rows(int n, const int32_t* first, const int32_t* end, int slack_min,
                                                       int slack_pct, int32_t* row_len, int32_t* row_sorted,
-                                                      int64_t* size) {
+                                                      int64_t* size, BuildCounts* bc) {
     const int v = blockIdx.x * BLOCK + threadIdx.x;
     if (v >= n) return;
     const int len = end[v] - first[v];
+    if (len > CUT_LONG) bc->long_rows = 1;
     const long long sl = ((long long)len * slack_pct + 99) / 100;
     row_len[v] = len;
     row_sorted[v] = len;
@@ -400,7 +403,7 @@ mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int
     k_merge_scan<<<1, BLOCK, 0, st>>>(mtile, tiles, bc);
     k_merge<<<tiles, BLOCK, 0, st>>>(key[cur], val[cur], count, mtile, bits, mkey, sum, first, end);
     k_build_rows<<<blocks_for(n, BLOCK), BLOCK, 0, st>>>(n, first, end, slack_min, slack_pct, out->row_len,
-                                                         out->row_sorted, size);
+                                                         out->row_sorted, size, bc);
     launch_scan_sizes(n, size, start, tile, st);
     BUILD_HIP(hipGetLastError());
     int64_t S = 0;
@@ -430,6 +433,7 @@ mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int
     out->slots = S;
     out->pairs = c.entries;
     out->m_unique = (int64_t)c.with_capacity;
+    out->long_rows = c.long_rows != 0;
     return MF_OK;
 #undef BUILD_HIP
 }

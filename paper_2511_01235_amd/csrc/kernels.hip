@@ -3046,29 +3046,37 @@ __global__ void __launch_bounds__(BS) k_batch_cleanup_multi(GraphUpdates* gu) {
 // ---- cut certificate --------------------------------------------------------
 
 // Bound by its longest rows, so the slots are shared out, not the vertices: a
-// workgroup prefix-sums the row lengths of its 256 vertices and consecutive
+// workgroup prefix-sums the row lengths of its vertices and consecutive
 // threads take consecutive slots, four in flight each, the neighbour's height
 // gathered only where there is capacity.  Rows above CUT_LONG slots go to a
 // list that a second launch takes one workgroup per row: power-law graphs
 // have them side by side, and all of a workgroup's together would decide the
 // time.  (RMAT-18, one row of 26,000 slots: a thread per row 6.1 ms, shared
-// out without the list 1.2 ms, both launches
-// 0.13.)
+// out without the list 1.2 ms, both launches 0.13.)  The second launch costs
+// a cut without such rows 5 us of 47, so the caller leaves it out where the
+// last cut, or the load, saw none, and looks at the count.
+// A workgroup stages about CUT_SHARE slots' vertices (its threads have two
+// slots each in flight), at least CUT_PER_MIN of them, so that a small graph is
+// spread over the chip; above 1024 workgroups of 256 vertices they loop.
+// (mf_min_cut of ER graphs of 4,000 and 16,000 vertices of degree 8: 49 and 48
+// us with a thread per row, 60 and 66 with 256 vertices a workgroup and the
+// second launch always there, 45 and 48 now.)
 constexpr int CUT_U = 4;
-constexpr int CUT_LONG = 256;
 constexpr int CUT_BLOCK = 256;
+constexpr int CUT_PER_MIN = 16;
+constexpr int64_t CUT_SHARE = 512;
 
 __global__ void __launch_bounds__(CUT_BLOCK) k_cut(DevGraph g, uint8_t* side, unsigned long long* cut,
-                                                   int32_t* long_rows, int32_t* long_count) {
+                                                   int32_t* long_rows, int32_t* long_count, int per) {
     constexpr int BS = CUT_BLOCK;
     __shared__ int s_beg[BS], s_pre[BS + 1], s_w[BS / WAVE];
     const int N = g.n;
     const int tid = threadIdx.x;
     long long c = 0;
-    for (int base = blockIdx.x * BS; base < N; base += gridDim.x * BS) {
+    for (int base = blockIdx.x * per; base < N; base += gridDim.x * per) {
         const int v = base + tid;
         int len = 0;
-        if (v < N) {
+        if (tid < per && v < N) {
             const bool a = g.h[v] == N;
             side[v] = a ? 1 : 0;
             if (a) {
@@ -3995,8 +4003,13 @@ void launch_check_invariants(const DevGraph& g, unsigned long long* out, hipStre
 void launch_cut(const DevGraph& g, uint8_t* side, unsigned long long* cut, int32_t* rows, hipStream_t st) {
     int32_t* count = reinterpret_cast<int32_t*>(cut + 1);
     launch_fill_i32(reinterpret_cast<int32_t*>(cut), 0, 4, st);
-    k_cut<<<grid_for(g.n, CUT_BLOCK, 4096), CUT_BLOCK, 0, st>>>(g, side, cut, rows, count);
-    k_cut_long<<<grid_for(g.n, 1, 2048), CUT_BLOCK, 0, st>>>(g, cut, rows, count);
+    const int64_t want = std::max<int64_t>(g.n / 1024, CUT_SHARE * g.n / std::max<int64_t>(1, g.used_slots));
+    const int per = (int)std::max<int64_t>(CUT_PER_MIN, std::min<int64_t>(CUT_BLOCK, want));
+    k_cut<<<grid_for(g.n, per, 4096), CUT_BLOCK, 0, st>>>(g, side, cut, rows, count, per);
+}
+
+void launch_cut_long(const DevGraph& g, unsigned long long* cut, const int32_t* rows, hipStream_t st) {
+    k_cut_long<<<grid_for(g.n, 1, 2048), CUT_BLOCK, 0, st>>>(g, cut, rows, reinterpret_cast<const int32_t*>(cut + 1));
 }
 
 void launch_batch_solve(GraphSlot* slots, const int32_t* order, int num, int mode, const GrTune& tune,

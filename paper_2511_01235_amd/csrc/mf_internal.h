@@ -304,8 +304,12 @@ void launch_batch_clamp(const DevGraph& g, const mf_update* upd, int64_t k,
 // ctr not null: skipped when a row ran out of room (its demand stays in need[])
 void launch_batch_cleanup(BatchTable tb, int32_t* need, const int32_t* slot_of, int32_t* win,
                           int64_t k, const DevCounters* ctr, hipStream_t st);
-// side[v] = 1 where h[v] == n; cut[0] the capacity from there to the rest (cut[1] and rows[n]: scratch)
+// side[v] = 1 where h[v] == n; cut[0] the capacity from there to the rest, but
+// for the rows of more than CUT_LONG slots: their count (int32) goes to cut[1]
+// and they to rows[n], for launch_cut_long to add (nothing if there are none)
+constexpr int CUT_LONG = 256;
 void launch_cut(const DevGraph& g, uint8_t* side, unsigned long long* cut, int32_t* rows, hipStream_t st);
+void launch_cut_long(const DevGraph& g, unsigned long long* cut, const int32_t* rows, hipStream_t st);
 // out[8] (device): negative residuals, broken pair sums, broken pair links,
 // excess mismatches, sum of excesses, heights out of range, steep residual
 // slots, active vertices
@@ -454,6 +458,7 @@ struct DeviceBiCSR {
     int32_t *row_ptr = nullptr, *row_len = nullptr, *row_sorted = nullptr;  // the caller's: n + 1, n and n words
     SlotArrays a{nullptr, nullptr, nullptr, nullptr};                       // allocated here, the caller's to release
     int64_t slots = 0, pairs = 0, m_unique = 0;
+    bool long_rows = false;                                                 // a row of more than CUT_LONG slots
 };
 // The same graph as build_bicsr with res = cap, on the device; arguments
 // checked by bicsr_arguments_ok.  Same errors, MF_ERR_OUT_OF_MEMORY (*no_room:

@@ -140,3 +140,23 @@ def test_bitmap_that_does_not_fit_in_lds_is_left_out(device):
     want = oracle.DynOracle(n, *e, 0, n - 1).static()
     with mf.MaxFlowGraph(n, *e, 0, n - 1, bfs_lds_bitmap=1) as G:
         assert want > 0 and G.maxflow() == want
+
+
+@pytest.mark.gpu
+def test_cut_of_rows_that_grow_past_the_long_limit(device):
+    """Rows of 256 slots at the load and at the first cut, of more after a
+    batch of inserts, and after a batch that only changes capacities."""
+    width = 256
+    g = ring_layers(width, 1, 3, 63500)          # s: one slot per vertex of the first layer
+    u = np.zeros(9, np.int32)
+    v = (1 + width + np.arange(9)).astype(np.int32)
+    c = np.full(9, 25, np.int32)
+    o = oracle.DynOracle(g.n, g.src, g.dst, g.cap, g.s, g.t)
+    with mf.MaxFlowGraph(g.n, g.src, g.dst, g.cap, g.s, g.t) as G:
+        want = o.static()
+        assert G.maxflow() == want and G.min_cut()[1] == want
+        for batch in ((u, v, c), (u, v, c - 20), (u[:0], v[:0], c[:0])):
+            want = o.apply(*batch)
+            assert G.apply_batch(*batch) == want
+            side, cut = G.min_cut()
+            assert cut == want and side[g.s] == 1 and side[g.t] == 0
