@@ -370,12 +370,17 @@ mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int
     carve(a, &in, key, val, &hist, &totals, &sum, &first, &end, &size, &start, &tile, &mtile, &bc);
     // given back in the stream's order (hipFree would wait for the whole
     // device: a load beside a 125 ms kernel of another stream took 125 ms,
-    // 4 ms this way); the wait lets the pool return it to the device
+    // 4 ms this way); the wait behind it lets the pool return it to the device
     struct Release {
         void* p;
         hipStream_t st;
+        void give_back() {
+            if (p) (void)hipFreeAsync(p, st);
+            p = nullptr;
+        }
         ~Release() {
-            (void)hipFreeAsync(p, st);
+            if (!p) return;
+            give_back();
             (void)hipStreamSynchronize(st);
         }
     } release{block, st};
@@ -428,6 +433,7 @@ mf_status build_bicsr_device(int32_t n, int64_t m, const int32_t* src, const int
                                                                   out->row_ptr, out->a, bc);
     BUILD_HIP(hipGetLastError());
     BUILD_HIP(hipMemcpyAsync(&c, bc, sizeof(c), hipMemcpyDeviceToHost, st));
+    release.give_back();  // (behind the copy; one wait for both)
     BUILD_HIP(hipStreamSynchronize(st));
     if (c.overflow) return MF_ERR_OVERFLOW;
     out->slots = S;
